@@ -87,7 +87,8 @@ typedef struct pipe_plan_info {
     size_t spectra_bytes;    /* device bytes held by the plan's Green spectra               */
     double model_bytes;      /* algorithmic HBM bytes of one solve (all passes)             */
     double pass_bytes[5];    /* the same per pass: z-forward, y-forward, x+product,         */
-                             /* y-inverse, z-inverse                                        */
+                             /* y-inverse, z-inverse; in the sine modes x, y sines, z       */
+                             /* convolution, y, x sines back                                */
     double build_ms;         /* wall time of the plan build (Green evaluation + spectra)    */
     double tune_ms;          /* PIPE_AUTOTUNE: the chosen lengths' measured ms per solve  */
                              /* (0 = taken from the cache; -1 = not tuned)                */
@@ -133,9 +134,17 @@ pipe_status_t pipe_green_plan(int nx, int ny, int nz, double hx, double hy, doub
  * MI355X, so a slow factorisation (432 = 27 * 16) gives way to a fast one
  * (512) when that is quicker overall; below 64 it is the smallest length.
  * The physical result does
- * not depend on the padded lengths.  hip_stream (a hipStream_t, may be NULL) orders the plan build's GPU
+ * not depend on the padded lengths.
+ * A mesh that fills the pipe's lattice in x and y (nx hx = a or (nx + 1) hx = a
+ * to rounding, no offset, likewise in y, nx, ny <= 512) with all lengths left
+ * at 0 is solved in the discrete sine modes of the cross-section instead, where
+ * the four terms are one real factor per mode and nothing is padded in x and y:
+ * the same potential to rounding, in about a third of the memory traffic.  Such
+ * a plan reports the lengths and workspace the padded transform would have, and
+ * 0 for the launch schedule (xtile, apad, zblocks, xnt, a1pad); explicit lengths
+ * or a forced PIPE_SCHEDULE keep the padded transform.  hip_stream (a hipStream_t, may be NULL) orders the plan build's GPU
  * work; the call still returns only when the build has finished.
- * Every 3-D plan (here, pipe_green_plan_region, pipe_free_plan) also picks a
+ * Every other 3-D plan (here, pipe_green_plan_region, pipe_free_plan) also picks a
  * launch schedule by timing the solve on scratch buffers during the build:
  * the kz tile of the x pass (its widest or half of it), the row pitch of the
  * y-transformed array (lz/2 plus 0, 16 or 32), the block cap of the z
@@ -355,6 +364,8 @@ pipe_status_t pipe_plan_green_table(pipe_plan_t plan, void* out_device, void* hi
  *   plane 0 = Re T_cc(kx,ky,kz); planes 1,2 = T_cr(kx,ky,kz);
  *   planes 3,4 = T_rc(kx,ky,kz); planes 5,6 = T_rr(kx,ky,kz);
  *   planes 7,8 = T_rr(lx-kx,ky,kz)   (re, im pairs).
+ * A plan that solves in the sine modes builds these spectra for the call
+ * (temporary device memory; OUT_OF_MEMORY if there is none).
  * A free-space plan (pipe_free_plan) has only plane 0 (T_cc of G = 1/r);
  * planes 1..8 of its copy are zero.
  * For a banded plan (pipe_green_plan_banded) the copy is the plan's own

@@ -268,6 +268,93 @@ __global__ void untile_kernel(const T_* __restrict__ table, const T_* __restrict
     }
 }
 
+// ---------------------------------------------------------------- sine modes
+
+// m' of stored mode p (odd ones first).
+__device__ __forceinline__ int stored_mode(int p, int no) { return p < no ? 2 * p + 1 : 2 * (p - no) + 2; }
+
+// sin(pi t / N) for integer t: reduced modulo 2N exactly, then to the first quadrant.
+__device__ __forceinline__ double sin_lattice(long t, int N) {
+    long u = t % (2L * N);
+    double sg = 1.0;
+    if (u > N) {
+        u = 2L * N - u;
+        sg = -1.0;
+    }
+    if (2 * u > N) u = N - u;
+    return sg * sinpi((double)u / (double)N);
+}
+
+// Operand layout of modal.hip: [direction][parity][row tile][16-deep block][load][lane][value]
+// with VA = 16 / sizeof(T) values per load; value e of load q holds depth
+// 16 kb + 4 (q VA + e) + lane / 16 of row 16 rt + lane % 16.
+template <typename T>
+__global__ void sine_frag_kernel(T* out, int na, int nm) {
+    constexpr int VA = 16 / sizeof(T);
+    const int h = (na + 1) / 2, he = na / 2, no = (nm + 1) / 2, ne = nm / 2, N = na + 1;
+    const int th = (h + 15) / 16, tm = (no + 15) / 16;
+    const long half = 2L * th * tm * 256, i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 2 * half) return;
+    const int inv = i >= half;
+    long j = i - inv * half;
+    const int rt_n = inv ? th : tm, kb_n = inv ? tm : th;
+    const int e = (int)(j % VA);
+    j /= VA;
+    const int lane = (int)(j % 64);
+    j /= 64;
+    const int q = (int)(j % (4 / VA));
+    j /= 4 / VA;
+    const int kb = (int)(j % kb_n);
+    j /= kb_n;
+    const int rt = (int)(j % rt_n), par = (int)(j / rt_n);
+    const int row = rt * 16 + lane % 16, dep = kb * 16 + 4 * (q * VA + e) + lane / 16;
+    const int x = inv ? row : dep, m = inv ? dep : row;     // node, mode within its parity
+    const bool ok = par ? (x < he && m < ne) : (x < h && m < no);
+    const long mode = par ? 2L * m + 2 : 2L * m + 1;
+    out[i] = ok ? (T)sin_lattice(mode * (x + 1), N) : (T)0;
+}
+
+__global__ void modal_factors_kernel(double* out, int nax, int nmx, int nay, int nmy, int mx, int my, int rz, int nh,
+                                     double a, double b, double hz, int igf, double scale, long line0, long nlines) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nlines * (nh + 1)) return;
+    const int s = (int)(i % (nh + 1));
+    const long l = i / (nh + 1), line = line0 + l;
+    double w = 0.0;
+    if (s < rz) {
+        const int m1 = stored_mode((int)(line / nmy), (nmx + 1) / 2), n1 = stored_mode((int)(line % nmy), (nmy + 1) / 2);
+        const int px = 2 * (nax + 1), py = 2 * (nay + 1);
+        // the modes with the same sines on the lattice: m1, 2N - m1, 2N + m1, ...
+        for (int m = m1, fx = 0; m <= mx; m = fx ? m + 2 * m1 : m + px - 2 * m1, fx ^= 1)
+            for (int n = n1, fy = 0; n <= my; n = fy ? n + 2 * n1 : n + py - 2 * n1, fy ^= 1) {
+                const double km = (double)m / a, kn = (double)n / b;
+                const double kap = M_PI * sqrt(km * km + kn * kn);
+                w += (igf ? igf_g(kap * hz, s) : exp(-kap * ((double)s * hz))) / kap;
+            }
+        w *= scale;
+    }
+    double* row = out + l * 2 * nh;
+    row[s] = w;
+    if (s > 0 && s < nh) row[2 * nh - s] = w;
+}
+
+// Packed spectra of real even sequences (imaginary parts are rounding) -> pairs
+// ((t_k + t_{nh-k})/2, (t_k - t_{nh-k})/2) / (2 nh), k <= nh/2.
+template <typename T2, typename T>
+__global__ void modal_table_kernel(const double2* __restrict__ spec, T2* table, int nh, long nlines) {
+    const int np = nh / 2 + 1;
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nlines * np) return;
+    const int k = (int)(i % np);
+    const double2* s = spec + (i / np) * nh;
+    const double t0 = s[k].x, t1 = k == 0 ? s[0].y : s[nh - k].x;
+    const double c = 0.5 / (2.0 * nh);
+    T2 v;
+    v.x = (T)(c * (t0 + t1));
+    v.y = (T)(c * (t0 - t1));
+    table[i] = v;
+}
+
 // ---------------------------------------------------------------- launchers
 
 static inline unsigned blocks_for(long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -333,6 +420,34 @@ hipError_t launch_untile(const void* table, const void* nyq, void* out, int real
     else
         hipLaunchKernelGGL(untile_kernel<float>, dim3(blocks_for(n, 256)), dim3(256), 0, st, (const float*)table,
                            (const float*)nyq, (float*)out, lx, ly, nh, tile, nval);
+    return hipGetLastError();
+}
+
+hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStream_t st) {
+    const long n = (long)sine_frag_elems(na, nm);
+    if (real_bytes == 8)
+        hipLaunchKernelGGL(sine_frag_kernel<double>, dim3(blocks_for(n, 256)), dim3(256), 0, st, (double*)frag, na, nm);
+    else
+        hipLaunchKernelGGL(sine_frag_kernel<float>, dim3(blocks_for(n, 256)), dim3(256), 0, st, (float*)frag, na, nm);
+    return hipGetLastError();
+}
+
+hipError_t launch_modal_factors(double* out, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz, int nh,
+                                double a, double b, double hz, int igf, double scale, long line0, long nlines,
+                                hipStream_t st) {
+    hipLaunchKernelGGL(modal_factors_kernel, dim3(blocks_for(nlines * (nh + 1), 256)), dim3(256), 0, st, out, ax.na,
+                       ax.nm, ay.na, ay.nm, mx, my, rz, nh, a, b, hz, igf, scale, line0, nlines);
+    return hipGetLastError();
+}
+
+hipError_t launch_modal_table(const void* spec, void* table, int real_bytes, int nh, long nlines, hipStream_t st) {
+    const unsigned nb = blocks_for(nlines * (nh / 2 + 1), 256);
+    if (real_bytes == 8)
+        hipLaunchKernelGGL((modal_table_kernel<double2, double>), dim3(nb), dim3(256), 0, st, (const double2*)spec,
+                           (double2*)table, nh, nlines);
+    else
+        hipLaunchKernelGGL((modal_table_kernel<float2, float>), dim3(nb), dim3(256), 0, st, (const double2*)spec,
+                           (float2*)table, nh, nlines);
     return hipGetLastError();
 }
 

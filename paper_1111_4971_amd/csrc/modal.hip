@@ -1,0 +1,862 @@
+// modal.hip -- the solve in the discrete sine modes of the cross-section.
+//
+// On a mesh whose nodes fill the pipe's lattice (X_i = (i+1) a/N, i + 1 < N, the
+// same in y) the four-term operator of Eq. 8 is diagonal in x and y: the four
+// cosines of each mode (m, n) combine to
+//   4 sin(m pi X/a) sin(m pi X'/a) sin(n pi Y/b) sin(n pi Y'/b),
+// and on the lattice the modes m, 2N - m, 2N + m, ... have the same sines up to
+// sign, so they fold onto m' = 1 .. N - 1.  A solve is then
+//   M1 x sine transform  (nx, ny, nz)   -> (nmx, ny, nzp)      [sine]
+//   M2 y sine transform  (nmx, ny, nzp) -> (nmx, nmy, nzp)     [sine]
+//   M3 z convolution of every mode line with its folded z factor, in place
+//      (real lines zero-padded to lz, one real spectrum per line)   [zconv]
+//   M4 y sine transform back, M5 x sine transform back to (nx, ny, nz),
+// with nothing padded in x and y: 11 n values move instead of the 35 n of the
+// padded transform (n = nx ny nz, the spectra included).  nzp is nz rounded up
+// to a 16-byte vector.
+#include <algorithm>
+
+#include "pass_common.h"
+
+#if !defined(PIPE_TU) || PIPE_TU == 1
+#define PIPE_TU_FP32 1
+#endif
+#if !defined(PIPE_TU) || PIPE_TU == 2
+#define PIPE_TU_FP64 1
+#endif
+
+namespace pipe {
+
+// ---------------------------------------------------------------- sine transform
+//
+// The sine matrix of odd m is even about the middle of the lattice, that of even
+// m odd, so each transform is two half-size products (folded: half the
+// multiplications): with s_i = x_i + x_{na-1-i}, d_i = x_i - x_{na-1-i}, i < na/2,
+//   y_m = sum_i sin(m pi (i+1)/N) s_i (m odd),  sum_i sin(..) d_i (m even);
+// back, x_i = E_i + O_i and x_{na-1-i} = E_i - O_i from the two sums over m.
+// N = na + 1 has large prime factors on the usual meshes (129 = 3 43, 257), so
+// the products run on the matrix cores, in the working precision.
+
+template <typename real, int V> struct vec_t { typedef real type __attribute__((ext_vector_type(V))); };
+template <typename real> struct vec_t<real, 1> { typedef real type; };
+template <typename real, int V> using vecv = typename vec_t<real, V>::type;
+
+// 16 x 16 x 4 matrix instruction: A[lane % 16][lane / 16], B[lane / 16][lane % 16];
+// register r of the result holds row(lane, r), column lane % 16.
+template <typename real> struct Mfma16;
+template <> struct Mfma16<float> {
+    typedef float acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ acc mac(float a, float b, acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static constexpr int STEP = 1;   // rows between the registers of a lane
+    static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
+template <> struct Mfma16<double> {
+    typedef double acc __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ acc mac(double a, double b, acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static constexpr int STEP = 4;
+    static __device__ __forceinline__ int row(int lane, int r) { return (lane >> 4) + 4 * r; }
+};
+
+template <typename real, int V> __device__ __forceinline__ real velem(const vecv<real, V>& v, int e) {
+    if constexpr (V == 1) return v;
+    else return v[e];
+}
+template <typename real, int V> __device__ __forceinline__ void vset(vecv<real, V>& v, int e, real x) {
+    if constexpr (V == 1) v = x;
+    else v[e] = x;
+}
+
+// What both kernels below share: the operand access and the block's arithmetic.
+// UV: the user's array (input of the forward, output of the inverse transform) is
+// accessed as vectors; else value by value, bounded by nz.  Arrays are addressed as
+// a uniform base and a 32-bit byte offset (the launcher checks that they fit).
+template <typename real, bool INV, int V, bool UV> struct Sine {
+    using vec = vecv<real, V>;
+    using M = Mfma16<real>;
+    using acc_t = typename M::acc;
+    static constexpr int VA = 16 / sizeof(real), NA = 4 / VA;   // A values per load, loads per 16-deep block
+    using veca = vecv<real, VA>;
+
+    // Vector column cg = slab wv + g of the z rows.
+    struct Column {
+        unsigned slab, g;
+        __device__ __forceinline__ Column(unsigned cg, unsigned wv) : slab(cg / wv), g(cg % wv) {}
+        __device__ __forceinline__ void advance(unsigned dslab, unsigned dg, unsigned wv) {
+            slab += dslab;
+            g += dg;
+            if (g >= wv) {
+                g -= wv;
+                ++slab;
+            }
+        }
+        __device__ __forceinline__ unsigned offset(unsigned ss_bytes) const {
+            return slab * ss_bytes + g * (unsigned)(V * sizeof(real));
+        }
+    };
+    static __device__ __forceinline__ vec load(const SineArgs& a, gptr<const char> base, unsigned off, unsigned g, bool ok) {
+        if constexpr (INV || UV) {
+            return *reinterpret_cast<gptr<const vec>>(base + off);
+        } else {
+            const gptr<const real> p = reinterpret_cast<gptr<const real>>(base + off);
+            vec v{};
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (ok && (int)g * V + e < a.nz) vset<real, V>(v, e, p[e]);
+            return v;
+        }
+    }
+    static __device__ __forceinline__ void store(const SineArgs& a, gptr<char> base, unsigned off, unsigned g, const vec& v) {
+        if constexpr (!INV || UV) {
+            *reinterpret_cast<gptr<vec>>(base + off) = v;
+        } else {
+            const gptr<real> p = reinterpret_cast<gptr<real>>(base + off);
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if ((int)g * V + e < a.nz) p[e] = velem<real, V>(v, e);
+        }
+    }
+    // Sums of a product over the 16-deep blocks: each block is two 8-deep chains from
+    // zero (one rounding per product, on partial sums of 8 terms) and the chains are
+    // added pairwise.  One plain chain over the whole depth left FP32 solves 1.2x
+    // (depth 64) to 2x (depth 128) further off than the padded transform.
+    //
+    // part[l] holds the sum of 2^l blocks; merge<KB> takes in block kb (compile-time after
+    // unrolling) like a binary counter, the last block everything into part[0].
+    static constexpr int LEVELS = 4;
+    template <int KB> static __device__ __forceinline__ void merge(int kb, acc_t t, acc_t (&part)[LEVELS][V], int c) {
+        int l = 0;
+#pragma unroll
+        for (int q = 0; q < LEVELS; ++q) {
+            if (q == l && ((kb >> q) & 1)) {
+                t = part[q][c] + t;
+                l = q + 1;
+            }
+        }
+        const bool last = kb + 1 == KB;
+        // what is left of the counter above level l
+#pragma unroll
+        for (int q = 0; q < LEVELS; ++q)
+            if (last && q >= l && ((kb >> q) & 1)) t = part[q][c] + t;
+#if defined(__HIP_DEVICE_COMPILE__)
+        // the additions are done here: left alone, the compiler moves those of all
+        // blocks past the last product and holds every chain's result until then
+        asm volatile("" : "+v"(t));
+#endif
+#pragma unroll
+        for (int q = 0; q < LEVELS; ++q)
+            if (q == (last ? 0 : l)) part[q][c] = t;
+    }
+    // forward: a 16-row tile of one parity's modes (i0 the lane's first row in it)
+    static __device__ __forceinline__ void put_modes(const SineArgs& a, int i0, int par, const acc_t* sum, gptr<char> out,
+                                                     unsigned col, unsigned g) {
+        const unsigned es = (unsigned)(a.out_es * sizeof(real)), o0 = col + (par ? a.no + i0 : i0) * es;
+        const int n = par ? a.ne : a.no;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            vec v;
+#pragma unroll
+            for (int c = 0; c < V; ++c) vset<real, V>(v, c, sum[c][r]);
+            if (i0 + r * M::STEP < n) store(a, out, o0 + r * M::STEP * es, g, v);
+        }
+    }
+    // inverse: a 16-row tile of nodes and its mirror image from the two parities' sums
+    static __device__ __forceinline__ void put_nodes(const SineArgs& a, int i0, const acc_t* so, const acc_t* se,
+                                                     gptr<char> out, unsigned col, unsigned g) {
+        const unsigned es = (unsigned)(a.out_es * sizeof(real)), o0 = col + i0 * es, m0 = col + (a.na - 1 - i0) * es;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + r * M::STEP;
+            vec o, e;
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                vset<real, V>(o, c, so[c][r]);
+                vset<real, V>(e, c, se[c][r]);
+            }
+            if (i < a.he) {
+                store(a, out, o0 + r * M::STEP * es, g, o + e);
+                store(a, out, m0 - r * M::STEP * es, g, o - e);
+            } else if (i < a.h) {
+                store(a, out, o0 + r * M::STEP * es, g, o);
+            }
+        }
+        // a node row on the wall (na = n - 1) carries no mode
+        if (i0 == 0 && a.na < a.n) store(a, out, col + a.na * es, g, vec{});
+    }
+};
+
+// Persistent: block b takes tiles b, b + grid, ... of g 16-lane column groups (V
+// columns a lane) and all rows.  Wave w < rt g owns row tile w % rt of column
+// group w / rt and keeps that tile's matrix rows (both parities, KB 16-deep
+// blocks) in registers.  Rows come two tiles ahead: loaded into registers during
+// the products of one tile, written to the free LDS buffer, folded (forward),
+// during those of the next (its first half of waves after the odd modes, the other
+// half, which shares the SIMDs, before them, so that the matrix cores are not left
+// idle), used in the one after.  Column tile c of a group is the columns V j + c
+// (j = lane % 16), so the B operands of all V tiles come with one LDS vector read
+// and a row of the result leaves as one vector a lane, 16 lanes contiguous.
+template <typename real, bool INV, int V, int KB, bool UV>
+__global__ __launch_bounds__(512) void sine_kernel(SineArgs a, const GroupArgs* __restrict__ group) {
+    using S = Sine<real, INV, V, UV>;
+    using M = typename S::M;
+    using vec = typename S::vec;
+    using veca = typename S::veca;
+    using acc_t = typename S::acc_t;
+    const void* in = a.in;
+    void* out = a.out;
+    if (group) {
+        in = group[blockIdx.z].in;
+        out = group[blockIdx.z].out;
+    }
+    extern __shared__ __align__(16) unsigned char smem[];
+    vec* lds = reinterpret_cast<vec*>(smem);           // [buffer][column group][parity][16 KB rows][16]
+    constexpr int KP = 16 * KB;
+    const gptr<const char> gin = to_global((const char*)in);
+    const gptr<char> gout = to_global((char*)out);
+    const int gw = a.g * 16, buf = a.g * 2 * KP * 16;
+    const int cl = threadIdx.x % gw, r0 = threadIdx.x / gw, rs = blockDim.x / gw;   // 4 rs >= KP
+    // rows of the two halves: forward i and its mirror image (folded here),
+    // backward mode 2i + 1 and mode 2i + 2; zero beyond the half sizes
+    const int na_ = INV ? a.no : a.h, nb_ = INV ? a.ne : a.he;
+    const unsigned ies = (unsigned)(a.in_es * sizeof(real)), iss = (unsigned)(a.in_ss * sizeof(real));
+    const unsigned xo = r0 * ies, yo = (INV ? a.no + r0 : a.na - 1 - r0) * ies;
+    const unsigned tiles = (unsigned)((a.ngroups + gw - 1) / gw), wv = (unsigned)a.wv;
+    const unsigned dslab = gridDim.x * gw / wv, dg = gridDim.x * gw % wv;
+    vec x[4], y[4];
+    typename S::Column cin(blockIdx.x * gw + cl, wv);
+    unsigned fetched = blockIdx.x;      // the tile the next fetch takes
+    auto fetch = [&] {
+        // column 0 stands in for one past the end, row 0 for an absent row: no branch,
+        // and nothing here uses the values, so the loads stay in flight
+        const bool act = fetched * gw + cl < (unsigned)a.ngroups;
+        const unsigned g = act ? cin.g : 0, col = act ? cin.offset(iss) : 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = r0 + u * rs;
+            x[u] = S::load(a, gin, col + (i < na_ ? xo + u * rs * ies : 0), g, act && i < na_);
+            y[u] = S::load(a, gin, col + (i < nb_ ? (INV ? yo + u * rs * ies : yo - u * rs * ies) : 0), g, act && i < nb_);
+        }
+        cin.advance(dslab, dg, wv);
+        fetched += gridDim.x;
+    };
+    auto stage = [&](vec* l) {
+        l += (cl / 16) * 2 * KP * 16 + cl % 16;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = r0 + u * rs;
+            if (i < nb_) {
+                l[i * 16] = INV ? x[u] : x[u] + y[u];
+                l[(KP + i) * 16] = INV ? y[u] : x[u] - y[u];
+            } else if (i < na_) {
+                l[i * 16] = x[u];
+            }
+        }
+    };
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const bool works = wave < a.rt * a.g;
+    const int rt = wave % a.rt, gi = works ? wave / a.rt : 0;
+    const int i0 = rt * 16 + M::row(lane, 0);
+    fetch();
+    veca A[2][KB][S::NA];
+    const gptr<const veca> frag = reinterpret_cast<gptr<const veca>>(to_global((const real*)a.frag));
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int q = 0; q < S::NA; ++q) A[p][kb][q] = frag[(((long)p * a.rt + rt) * KB + kb) * S::NA * 64 + q * 64 + lane];
+    // the rows past the half sizes, zero in both buffers from here on
+    for (int i = na_ + r0; i < KP; i += rs)
+        for (int q = 0; q < 2; ++q) lds[q * buf + ((cl / 16) * 2 * KP + i) * 16 + cl % 16] = vec{};
+    for (int i = nb_ + r0; i < KP; i += rs)
+        for (int q = 0; q < 2; ++q) lds[q * buf + ((cl / 16) * 2 * KP + KP + i) * 16 + cl % 16] = vec{};
+    stage(lds);
+    if (fetched < tiles) fetch();
+#if defined(__HIP_DEVICE_COMPILE__)
+    // wait for the matrix rows here: a wait inside the loop would also wait for the
+    // loads issued ahead there
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+            for (int q = 0; q < S::NA; ++q) asm volatile("" : "+v"(A[p][kb][q]));
+#endif
+    typename S::Column cout(blockIdx.x * gw + gi * 16 + (lane & 15), wv);
+    const unsigned oss = (unsigned)(a.out_ss * sizeof(real));
+    const int turn = (wave / 4) & 1 ? 0 : 1;
+    int cur = 0;
+    for (unsigned tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        __syncthreads();
+        const vec* b = lds + cur * buf + gi * 2 * KP * 16 + (lane >> 4) * 16 + (lane & 15);
+        const bool act = works && tile * gw + gi * 16 + (lane & 15) < (unsigned)a.ngroups;
+        const unsigned col = cout.offset(oss);
+        acc_t odd[V];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            if (p == turn && tile + gridDim.x < tiles) {
+                stage(lds + (cur ^ 1) * buf);
+                if (fetched < tiles) fetch();
+            }
+            if (!works) continue;
+            // MFMAs of one column tile, then the additions of the one before (done by
+            // then, and in the shadow of these): the order is fixed by the barriers
+            acc_t part[S::LEVELS][V], c0, c1, d0, d1;
+            vec bc[4], bn[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) bc[s] = b[(p * KP + 4 * s) * 16];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                const veca* af = A[p][kb];
+#pragma unroll
+                for (int c = 0; c < V; ++c) {
+                    c0 = M::mac(af[0][0], velem<real, V>(bc[0], c), acc_t{});
+                    c1 = M::mac(af[2 / S::VA][2 % S::VA], velem<real, V>(bc[2], c), acc_t{});
+                    c0 = M::mac(af[1 / S::VA][1 % S::VA], velem<real, V>(bc[1], c), c0);
+                    c1 = M::mac(af[3 / S::VA][3 % S::VA], velem<real, V>(bc[3], c), c1);
+                    if (c == 0 && kb + 1 < KB) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) bn[s] = b[(p * KP + (kb + 1) * 16 + 4 * s) * 16];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (kb + c > 0) S::template merge<KB>(c ? kb : kb - 1, d0 + d1, part, c ? c - 1 : V - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    d0 = c0;
+                    d1 = c1;
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) bc[s] = bn[s];
+            }
+            S::template merge<KB>(KB - 1, d0 + d1, part, V - 1);
+            if constexpr (INV) {
+                if (p == 0) {
+#pragma unroll
+                    for (int c = 0; c < V; ++c) odd[c] = part[0][c];
+                } else if (act) {
+                    S::put_nodes(a, i0, odd, part[0], gout, col, cout.g);
+                }
+            } else if (act) {
+                S::put_modes(a, i0, p, part[0], gout, col, cout.g);
+            }
+        }
+        cout.advance(dslab, dg, wv);
+        cur ^= 1;
+    }
+}
+
+// The same with the matrix read from L2 one 16-deep block ahead, for depths whose
+// rows do not fit the registers: one tile per block, waves over its row tiles.
+template <typename real, bool INV, int V, bool UV>
+__global__ __launch_bounds__(512) void sine_stream_kernel(SineArgs a, const GroupArgs* __restrict__ group) {
+    using S = Sine<real, INV, V, UV>;
+    using M = typename S::M;
+    using vec = typename S::vec;
+    using veca = typename S::veca;
+    using acc_t = typename S::acc_t;
+    const void* in = a.in;
+    void* out = a.out;
+    if (group) {
+        in = group[blockIdx.z].in;
+        out = group[blockIdx.z].out;
+    }
+    extern __shared__ __align__(16) unsigned char smem[];
+    vec* lds = reinterpret_cast<vec*>(smem);           // [parity][16 kb rows][16]
+    const int kp = a.kb * 16;
+    const unsigned wv = (unsigned)a.wv;
+    const gptr<const char> gin = to_global((const char*)in);
+    const gptr<char> gout = to_global((char*)out);
+    {
+        const int cl = threadIdx.x % 16, r0 = threadIdx.x / 16, rs = blockDim.x / 16;
+        const unsigned cg = blockIdx.x * 16 + cl;
+        const bool act = cg < (unsigned)a.ngroups;
+        const typename S::Column c(act ? cg : 0, wv);
+        const unsigned es = (unsigned)(a.in_es * sizeof(real)), col = c.offset((unsigned)(a.in_ss * sizeof(real)));
+        const int na_ = INV ? a.no : a.h, nb_ = INV ? a.ne : a.he;
+        constexpr int U = 4;
+        for (int ib = r0; ib < kp; ib += U * rs) {
+            vec x[U], y[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = ib + u * rs;
+                x[u] = S::load(a, gin, col + (i < na_ ? i * es : 0), c.g, act && i < na_);
+                y[u] = S::load(a, gin, col + (i < nb_ ? (INV ? a.no + i : a.na - 1 - i) * es : 0), c.g, act && i < nb_);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = ib + u * rs;
+                if (i < kp) {
+                    const vec xv = i < na_ ? x[u] : vec{}, yv = i < nb_ ? y[u] : vec{};
+                    lds[i * 16 + cl] = INV ? xv : xv + yv;
+                    lds[(kp + i) * 16 + cl] = INV ? yv : (i < nb_ ? xv - yv : vec{});
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64, nw = blockDim.x / 64;
+    const gptr<const veca> frag = reinterpret_cast<gptr<const veca>>(to_global((const real*)a.frag));
+    const unsigned cg = blockIdx.x * 16 + (lane & 15);
+    const bool act = cg < (unsigned)a.ngroups;
+    const typename S::Column c(act ? cg : 0, wv);
+    const unsigned col = c.offset((unsigned)(a.out_ss * sizeof(real)));
+    for (int rt = wave; rt < a.rt; rt += nw) {
+        const int i0 = rt * 16 + M::row(lane, 0);
+        acc_t odd[V];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const gptr<const veca> f = frag + ((long)p * a.rt + rt) * a.kb * S::NA * 64 + lane;
+            const vec* b = lds + p * kp * 16 + (lane >> 4) * 16 + (lane & 15);
+            // 8-deep chains added up over 64, then those sums over the depth
+            acc_t sum[V], four[V];
+#pragma unroll
+            for (int c = 0; c < V; ++c) sum[c] = four[c] = acc_t{};
+            veca af[S::NA], an[S::NA];
+#pragma unroll
+            for (int q = 0; q < S::NA; ++q) af[q] = f[q * 64];
+            for (int kb = 0; kb < a.kb; ++kb) {
+                const int kn = kb + 1 < a.kb ? kb + 1 : kb;
+#pragma unroll
+                for (int q = 0; q < S::NA; ++q) an[q] = f[(kn * S::NA + q) * 64];
+                vec v[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) v[s] = b[(kb * 16 + 4 * s) * 16];
+#pragma unroll
+                for (int c = 0; c < V; ++c) {
+                    acc_t c0 = M::mac(af[0][0], velem<real, V>(v[0], c), acc_t{});
+                    acc_t c1 = M::mac(af[2 / S::VA][2 % S::VA], velem<real, V>(v[2], c), acc_t{});
+                    c0 = M::mac(af[1 / S::VA][1 % S::VA], velem<real, V>(v[1], c), c0);
+                    c1 = M::mac(af[3 / S::VA][3 % S::VA], velem<real, V>(v[3], c), c1);
+                    four[c] += c0 + c1;
+                }
+                if (kb % 4 == 3 || kb + 1 == a.kb) {
+#pragma unroll
+                    for (int c = 0; c < V; ++c) {
+                        sum[c] += four[c];
+                        four[c] = acc_t{};
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < S::NA; ++q) af[q] = an[q];
+            }
+            if constexpr (INV) {
+                if (p == 0) {
+#pragma unroll
+                    for (int c = 0; c < V; ++c) odd[c] = sum[c];
+                } else if (act) {
+                    S::put_nodes(a, i0, odd, sum, gout, col, c.g);
+                }
+            } else if (act) {
+                S::put_modes(a, i0, p, sum, gout, col, c.g);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------- z convolution
+//
+// In place on lines of n values (pitch apart): forward transform of the line
+// zero-padded to 2 NH, product with the line's real spectrum, inverse, first n
+// values kept.  The line is read as NH packed pairs Z; with e = Z_k + conj
+// Z_{NH-k}, o = -i W^k (Z_k - conj Z_{NH-k}) (twice the spectra of the even and
+// odd samples) the two bins k and NH - k of the half spectrum are (e +- o)/2,
+// their product with the spectra t_k, t_{NH-k} and the packing of the inverse
+// give
+//   A = p e + m o,  B = m e + p o,  p, m = (t_k +- t_{NH-k})/2,
+//   Z'_k = A + i W^{-k} B,  Z'_{NH-k} = conj(A - i W^{-k} B),
+// so one thread takes both bins, and the table holds the pairs (p, m) for
+// k <= NH/2 (scale factors included).  k = 0 is the pair (0, NH) by the same
+// formula, and Z'_{NH/2} = 2 p Z_{NH/2}.
+//
+// A line lies inside one wavefront (P = NH/E lanes, P divides 64), and after the
+// last stage lane t holds the bins t + q P, q < E, which are also the inputs of
+// the inverse transform's first stage.  The partner of bin t + q P is bin
+// E - 1 - q of lane P - t (lane 0: bin E - q of its own), so the product needs one
+// lane exchange each way and no pass through LDS.  Only the first half of the
+// packed pairs is ever non-zero (n <= NH) or kept.
+
+// Length plan: at most 12 values per thread, 16 at NH = 1024, which keeps the line
+// in one wavefront.
+template <typename real, int NH> constexpr int zc_V() { return NH == 1024 ? 0 : narrow_variant<NH>(sizeof(real) == 8 ? 8 : 12); }
+
+// Lines per block: 256 threads, fewer while their LDS exceeds 64 KB (FP64, NH = 1024).
+template <typename real, int NH> constexpr int zc_lines() {
+    int l = 256 / (NH / Plan<NH, zc_V<real, NH>()>::E);
+    while (l * lpad_len<z_pad<NH>()>(NH) * 2 * (int)sizeof(real) > 65536) l /= 2;
+    return l;
+}
+
+// Stage twiddles from LDS.
+template <class PL, typename TW> struct TwLds {
+    const TW* tw;
+    template <int s> __device__ __forceinline__ TW get(int t, int b, int r) const {
+        constexpr int NS = plan_ns<PL>(s), P = PL::LEN / PL::E;
+        return tw[stage_tw_offset<PL>(NS) + (r - 1) * NS + (t + b * P) % NS];
+    }
+};
+// The same held in registers: they do not change from line to line.
+template <class PL> constexpr int tw_slot(int s) {
+    int n = 0;
+    for (int i = 1; i < s; ++i) n += PL::E / PL::radix(i) * (PL::radix(i) - 1);
+    return n;
+}
+template <class PL, typename TW> struct TwRegs {
+    TW w[tw_slot<PL>(PL::S) > 0 ? tw_slot<PL>(PL::S) : 1];
+    template <int s> __device__ __forceinline__ TW get(int, int b, int r) const {
+        return w[tw_slot<PL>(s) + b * (PL::radix(s) - 1) + r - 1];
+    }
+    template <int s = 1> __device__ __forceinline__ void load(const TwLds<PL, TW>& from, int t) {
+        if constexpr (s < PL::S) {
+#pragma unroll
+            for (int b = 0; b < PL::E / PL::radix(s); ++b)
+#pragma unroll
+                for (int r = 1; r < PL::radix(s); ++r)
+                    w[tw_slot<PL>(s) + b * (PL::radix(s) - 1) + r - 1] = from.template get<s>(t, b, r);
+            load<s + 1>(from, t);
+        }
+    }
+};
+
+// DFT of R values of which only the first half is non-zero: the even outputs are
+// the half-size DFT of it, the odd ones that of the half times W_R^r.
+template <int R, typename C> __device__ __forceinline__ void dft_half_zero(C* v) {
+    using real = decltype(C::x);
+    if constexpr (R == 4 || R == 8 || R == 16) {
+        constexpr int H = R / 2;
+        C e[H], o[H];
+#pragma unroll
+        for (int r = 0; r < H; ++r) {
+            e[r] = v[r];
+            const real c[8] = {1, (real)0.92387953251128675612818318939679, (real)0.70710678118654752440084436210485,
+                               (real)0.38268343236508977172845998403040, 0, (real)-0.38268343236508977172845998403040,
+                               (real)-0.70710678118654752440084436210485, (real)-0.92387953251128675612818318939679};
+            const int q = r * (16 / R);   // W_16^q = cos(2 pi q/16) - i sin(2 pi q/16)
+            if (q == 0) o[r] = v[r];
+            else if (q == 4) o[r] = cmake<C>(v[r].y, -v[r].x);
+            else o[r] = cmul(v[r], cmake<C>(c[q], -(q < 4 ? c[4 - q] : c[q - 4])));
+        }
+        dft<H, false>(e);
+        dft<H, false>(o);
+#pragma unroll
+        for (int r = 0; r < H; ++r) {
+            v[2 * r] = e[r];
+            v[2 * r + 1] = o[r];
+        }
+    } else {
+        dft<R, false>(v);
+    }
+}
+
+// Stages s.. of a transform inside a wavefront, results left in v: value b R + r of
+// the last stage is bin t + (b + r E/R) P.  HALF: stage 0's inputs e >= N/2 are zero.
+template <class PL, int s, bool INV, bool HALF, typename C, typename Tw, typename Lds>
+__device__ __forceinline__ void wave_stages(C* v, int t, const Tw& tw, Lds lds) {
+    constexpr int R = PL::radix(s), NS = plan_ns<PL>(s), NB = PL::E / R;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        if constexpr (s > 0) {
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[b * R + r] = ctw<INV>(v[b * R + r], tw.template get<s>(t, b, r));
+        }
+        if constexpr (s == 0 && HALF) dft_half_zero<R>(&v[b * R]);
+        else dft<R, INV>(&v[b * R]);
+    }
+    if constexpr (s + 1 < PL::S) {
+        stage_store<PL, R, NS>(v, t, [&](int e, C x) { lds.set(e, x); });
+        line_sync<Sync::WAVE>();
+        stage_load<PL, PL::radix(s + 1)>(v, t, [&](int e) { return lds.get(e); });
+        line_sync<Sync::WAVE>();
+        wave_stages<PL, s + 1, INV, HALF>(v, t, tw, lds);
+    }
+}
+
+// The value of another lane (byte index 4 * lane).
+__device__ __forceinline__ float from_lane(float x, int idx) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(idx, __float_as_int(x)));
+}
+__device__ __forceinline__ double from_lane(double x, int idx) {
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(idx, __double2hiint(x)),
+                            __builtin_amdgcn_ds_bpermute(idx, __double2loint(x)));
+}
+
+template <typename real, int NH>
+__global__ __launch_bounds__((zc_lines<real, NH>() * (NH / Plan<NH, zc_V<real, NH>()>::E)))
+void zconv_kernel(real* data, long pitch, int n, long nlines, const cplx<real>* table, const twid<real>* __restrict__ tw,
+                  const twid<real>* __restrict__ tw2, const GroupArgs* __restrict__ group) {
+    using C = cplx<real>;
+    using TW = twid<real>;
+    if (group) {
+        data = (real*)group[blockIdx.z].out;
+        table = (const C*)group[blockIdx.z].table;
+    }
+    using PL = Plan<NH, zc_V<real, NH>()>;
+    constexpr int E = PL::E, P = NH / E, LPW = zc_lines<real, NH>(), H = E / 2;
+    static_assert(64 % P == 0 && E % 2 == 0 && NH % 2 == 0, "a line per wavefront, bins paired");
+    constexpr int R0 = PL::radix(0), NB0 = E / R0, RL = PL::radix(PL::S - 1), NBL = E / RL;
+    constexpr int LR = (R0 + 1) / 2, NL = NB0 * LR;          // inputs of stage 0 that may be non-zero
+    constexpr int PADN = lpad_len<z_pad<NH>()>(NH);
+    constexpr int NP = NH / 2 + 1;
+    constexpr bool TWR = sizeof(real) == 4 && tw_slot<PL>(PL::S) <= 16;   // stage twiddles in registers
+    __shared__ C lds[PL::S > 1 ? LPW * PADN : 1];
+    __shared__ TW s_tw[stage_tw_size<PL>() > 0 ? stage_tw_size<PL>() : 1];
+    stage_twiddles(s_tw, tw, stage_tw_size<PL>());
+    __syncthreads();
+    const int t = threadIdx.x % P, l = threadIdx.x / P;
+    const int peer = ((threadIdx.x & 63) - t + (P - t) % P) * 4;
+    LdsLine<C, z_pad<NH>()> view{lds + (PL::S > 1 ? l * PADN : 0)};
+    const TwLds<PL, TW> twl{s_tw};
+    TwRegs<PL, TW> twr;
+    if constexpr (TWR) twr.load(twl, t);
+    TW w2[H];
+#pragma unroll
+    for (int q = 0; q < H; ++q) w2[q] = tw2[t + q * P];
+    const long ngroups = (nlines + LPW - 1) / LPW;
+    const gptr<real> gd = to_global(data);
+    const gptr<const C> gt = to_global(table);
+    // packed pairs of stage 0 (first half), spectra pairs of the bins t + q P, q < E/2,
+    // and of bin NH/2
+    auto load = [&](C* v, C* pm, real& mid, long line) {
+        const bool active = line < nlines;
+        const gptr<const C> src = reinterpret_cast<gptr<const C>>(gd + (active ? line : 0) * pitch);
+#pragma unroll
+        for (int b = 0; b < NB0; ++b)
+#pragma unroll
+            for (int r = 0; r < LR; ++r) {
+                const int m = t + b * P + r * (NH / R0);
+                C x = cmake<C>(0, 0);
+                if (active && 2 * m < n) {
+                    x = src[m];                       // pitch is even, rows 16-byte aligned
+                    if (2 * m + 1 >= n) x.y = 0;
+                }
+                v[b * LR + r] = x;
+            }
+        const gptr<const C> tl = gt + (active ? line : 0) * NP;
+#pragma unroll
+        for (int q = 0; q < H; ++q) pm[q] = tl[t + q * P];
+        mid = tl[NH / 2].x;
+    };
+    C nxt[NL], pn[H];
+    real mn = 0;
+    long g = blockIdx.x;
+    if (g < ngroups) load(nxt, pn, mn, g * LPW + l);
+    for (; g < ngroups; g += gridDim.x) {
+        C v[E], pm[H];
+        const real mid = mn;
+#pragma unroll
+        for (int b = 0; b < NB0; ++b)
+#pragma unroll
+            for (int r = 0; r < R0; ++r) {
+                if (r < LR) v[b * R0 + r] = nxt[b * LR + r];
+                else v[b * R0 + r] = cmake<C>(0, 0);
+            }
+#pragma unroll
+        for (int q = 0; q < H; ++q) pm[q] = pn[q];
+        const long gn = g + gridDim.x;
+        if (gn < ngroups) load(nxt, pn, mn, gn * LPW + l);
+        if constexpr (TWR) wave_stages<PL, 0, false, true>(v, t, twr, view);
+        else wave_stages<PL, 0, false, true>(v, t, twl, view);
+        // bin q of this lane after the forward / before the inverse transform
+        auto out = [&](int q) -> C& { return v[(q % NBL) * RL + q / NBL]; };
+        C u[E];
+        auto inp = [&](int q) -> C& { return u[(q % NB0) * R0 + q / NB0]; };
+        C back[H];
+#pragma unroll
+        for (int q = 0; q < H; ++q) {
+            const C zk = out(q);
+            C zn;
+            if constexpr (P > 1) {
+                const C mine = out(E - 1 - q), own = out((E - q) % E);
+                zn.x = from_lane(mine.x, peer);
+                zn.y = from_lane(mine.y, peer);
+                if (t == 0) zn = own;
+            } else {
+                zn = out((E - q) % E);
+            }
+            zn = cconj(zn);
+            const C ev = cadd(zk, zn);
+            const C d = ctw<false>(csub(zk, zn), w2[q]);
+            const C od = cmake<C>(d.y, -d.x);                        // -i W^k (Z_k - conj Z_{NH-k})
+            const real p = pm[q].x, m = pm[q].y;
+            const C A = cmake<C>(fma(p, ev.x, m * od.x), fma(p, ev.y, m * od.y));
+            const C B = ctw<true>(cmake<C>(fma(m, ev.x, p * od.x), fma(m, ev.y, p * od.y)), w2[q]);
+            inp(q) = cmake<C>(A.x - B.y, A.y + B.x);                 // A + i W^{-k} B
+            back[q] = cmake<C>(A.x + B.y, B.x - A.y);                // conj(A - i W^{-k} B)
+        }
+        const C half = cscale(out(H), 2 * mid);                      // lane 0: bin NH/2
+#pragma unroll
+        for (int i = H; i < E; ++i) {
+            C own = half;
+            if (i > H) own = back[E - i];
+            if constexpr (P > 1) {
+                C z;
+                z.x = from_lane(back[E - 1 - i].x, peer);
+                z.y = from_lane(back[E - 1 - i].y, peer);
+                if (t == 0) z = own;
+                inp(i) = z;
+            } else {
+                inp(i) = own;
+            }
+        }
+        if constexpr (TWR) wave_stages<PL, 0, true, false>(u, t, twr, view);
+        else wave_stages<PL, 0, true, false>(u, t, twl, view);
+        const long line = g * LPW + l;
+        const bool active = line < nlines;
+        const gptr<C> dst = reinterpret_cast<gptr<C>>(gd + (active ? line : 0) * pitch);
+#pragma unroll
+        for (int b = 0; b < NBL; ++b)
+#pragma unroll
+            for (int r = 0; r < (RL + 1) / 2; ++r) {
+                const int m = t + b * P + r * (NH / RL);
+                if (active && 2 * m < n) dst[m] = u[b * RL + r];
+            }
+    }
+}
+
+// ---------------------------------------------------------------- launchers
+
+// Depth (16-deep blocks) up to which the matrix rows stay in registers, and the
+// columns a lane then holds: one 16-byte vector, half of it where FP64 rows take
+// 128 registers.
+constexpr int kSineBlocks = 8;
+template <typename real> constexpr int sine_V(int kb) {
+    return sizeof(real) == 4 ? (kb <= kSineBlocks ? 4 : 2) : (kb <= 4 ? 2 : 1);
+}
+
+template <typename real, bool INV, bool UV, int KB>
+static hipError_t launch_sine_kb(SineArgs a, hipStream_t s, const GroupArgs* group, int ngroup) {
+    constexpr int V = sine_V<real>(KB);
+    const int row_waves = a.rt > KB ? a.rt : KB;      // 4 row loads a thread and half
+    // column groups per block: at least four waves while the tiles cover the chip
+    a.g = 1;
+    while (a.g < 4 && row_waves * a.g < 4 && a.ngroups * ngroup / (32 * a.g) >= 512) a.g *= 2;
+    const int waves = row_waves * a.g;
+    const long lds = 2l * 2 * 16 * KB * a.g * 16 * V * sizeof(real);
+    // blocks that fit a CU: 160 KB of LDS, 8 waves (2 per SIMD) where the matrix
+    // rows fill the registers, 16 where they do not
+    const int fit = (int)std::max(1l, std::min(163840 / lds, (long)(KB * (int)sizeof(real) > 16 ? 8 : 16) / waves));
+    const long ntile = (a.ngroups + a.g * 16 - 1) / (a.g * 16);
+    const long cap = std::max(1l, 256l * fit / ngroup);
+    const dim3 grid((unsigned)std::min(ntile, cap), 1, (unsigned)ngroup);
+    if (lds > 65536) {
+        const hipError_t e = hipFuncSetAttribute((const void*)sine_kernel<real, INV, V, KB, UV>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((sine_kernel<real, INV, V, KB, UV>), grid, dim3(64 * waves), lds, s, a, group);
+    return hipGetLastError();
+}
+
+template <typename real, bool INV, bool UV>
+static hipError_t launch_sine_dir(SineArgs a, hipStream_t s, const GroupArgs* group, int ngroup) {
+    if (a.rt <= 8) {
+        switch (a.kb) {
+            case 1: return launch_sine_kb<real, INV, UV, 1>(a, s, group, ngroup);
+            case 2: return launch_sine_kb<real, INV, UV, 2>(a, s, group, ngroup);
+            case 3: return launch_sine_kb<real, INV, UV, 3>(a, s, group, ngroup);
+            case 4: return launch_sine_kb<real, INV, UV, 4>(a, s, group, ngroup);
+            case 5: return launch_sine_kb<real, INV, UV, 5>(a, s, group, ngroup);
+            case 6: return launch_sine_kb<real, INV, UV, 6>(a, s, group, ngroup);
+            case 7: return launch_sine_kb<real, INV, UV, 7>(a, s, group, ngroup);
+            case 8: return launch_sine_kb<real, INV, UV, 8>(a, s, group, ngroup);
+        }
+    }
+    // more than 256 rows on either side: half-width columns keep 2 x 16 kb rows in 64 KB
+    constexpr int V = 8 / sizeof(real);
+    a.g = 1;
+    a.wv = a.wv * sine_V<real>(a.kb) / V;
+    a.ngroups = a.ngroups * sine_V<real>(a.kb) / V;
+    const dim3 grid((unsigned)((a.ngroups + 15) / 16), 1, (unsigned)ngroup);
+    hipLaunchKernelGGL((sine_stream_kernel<real, INV, V, UV>), grid, dim3(512), 2u * 16 * a.kb * 16 * V * sizeof(real), s, a,
+                       group);
+    return hipGetLastError();
+}
+
+template <typename real>
+hipError_t launch_sine(const SineAxis& ax, bool inverse, const void* in, void* out, int nz, int nzp, long in_ss,
+                       long in_es, long out_ss, long out_es, long nslabs, bool user_vec, hipStream_t s,
+                       const GroupArgs* group, int ngroup) {
+    if (nslabs <= 0 || nz <= 0 || nzp < nz || ax.na < 1 || ax.na > kSineMaxRows || ax.nm < 1 || ax.nm > ax.na ||
+        nzp % (16 / (int)sizeof(real)))
+        return hipErrorInvalidValue;
+    // the kernels' 32-bit byte offsets
+    const long in_rows = inverse ? ax.nm : ax.na, out_rows = inverse ? ax.n : ax.nm;
+    if (((in_rows - 1) * in_es + (nslabs - 1) * in_ss + nzp) * (long)sizeof(real) >= (1l << 32) ||
+        ((out_rows - 1) * out_es + (nslabs - 1) * out_ss + nzp) * (long)sizeof(real) >= (1l << 32))
+        return hipErrorInvalidValue;
+    SineArgs a{};
+    a.in = in;
+    a.out = out;
+    a.in_ss = in_ss; a.in_es = in_es; a.out_ss = out_ss; a.out_es = out_es;
+    a.nz = nz;
+    a.n = ax.n; a.na = ax.na;
+    a.h = (ax.na + 1) / 2; a.he = ax.na / 2;
+    a.no = (ax.nm + 1) / 2; a.ne = ax.nm / 2;
+    const int rows = inverse ? a.h : a.no, depth = inverse ? a.no : a.h;
+    a.rt = (rows + 15) / 16;
+    a.kb = (depth + 15) / 16;
+    a.frag = (const char*)ax.frag + (inverse ? sine_frag_elems(ax.na, ax.nm, false) * sizeof(real) : 0);
+    const int v = sine_V<real>(a.kb);
+    a.wv = nzp / v;
+    a.ngroups = nslabs * a.wv;
+    if (inverse)
+        return user_vec ? launch_sine_dir<real, true, true>(a, s, group, ngroup)
+                        : launch_sine_dir<real, true, false>(a, s, group, ngroup);
+    return user_vec ? launch_sine_dir<real, false, true>(a, s, group, ngroup)
+                    : launch_sine_dir<real, false, false>(a, s, group, ngroup);
+}
+
+// Transform lengths of the z convolution (kZconvLengths).
+#define PIPE_FOR_EACH_ZCONV_N(X) \
+    X(8) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(768) X(1024)
+
+// Blocks of a kernel that run on one CU at once.  The persistent z convolution gets
+// exactly as many as run (a second, partly filled wave of blocks costs more than the
+// uneven shares: 256x256x1024 FP32 236 us at 768 = 3 a CU, 260 at 2048, 305 at 1024).
+static int resident_blocks(const void* kernel, int threads) {
+    int b = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kernel, threads, 0) != hipSuccess || b < 1) b = 4;
+    return b;
+}
+
+template <typename real>
+hipError_t launch_zconv(int nh, void* data, long pitch, int n, long nlines, const void* table, const TwiddleBank& twb,
+                        hipStream_t s, const GroupArgs* group, int ngroup) {
+    using C = cplx<real>;
+    const twid<real>* tw2 = twb.get<twid<real>>(2 * nh);
+    if (!tw2 || nlines <= 0 || n < 1 || n > nh || pitch < n || pitch % 2) return hipErrorInvalidValue;
+    switch (nh) {
+#define X(N_)                                                                                            \
+    case N_: {                                                                                           \
+        constexpr int V = zc_V<real, N_>(), LPW = zc_lines<real, N_>();                                  \
+        const twid<real>* tw = twb.stage<twid<real>>(N_, V);                                             \
+        if (!tw) return hipErrorInvalidValue;                                                            \
+        static const int fit = resident_blocks((const void*)zconv_kernel<real, N_>, LPW * (N_ / Plan<N_, V>::E)); \
+        const long ng = (nlines + LPW - 1) / LPW, cap = std::max(1l, 256l * fit / ngroup);               \
+        dim3 grid((unsigned)(ng < cap ? ng : cap), 1, (unsigned)ngroup);                                 \
+        hipLaunchKernelGGL((zconv_kernel<real, N_>), grid, dim3(LPW * (N_ / Plan<N_, V>::E)), 0, s,       \
+                           (real*)data, pitch, n, nlines,                                                \
+                           (const C*)table, tw, tw2, group);                                             \
+        return hipGetLastError();                                                                        \
+    }
+        PIPE_FOR_EACH_ZCONV_N(X)
+#undef X
+    }
+    return hipErrorInvalidValue;
+}
+
+#define PIPE_INST(real)                                                                                        \
+    template hipError_t launch_sine<real>(const SineAxis&, bool, const void*, void*, int, int, long, long, long, \
+                                          long, long, bool, hipStream_t, const GroupArgs*, int);          \
+    template hipError_t launch_zconv<real>(int, void*, long, int, long, const void*, const TwiddleBank&,         \
+                                           hipStream_t, const GroupArgs*, int);
+#if PIPE_TU_FP32
+PIPE_INST(float)
+#endif
+#if PIPE_TU_FP64
+PIPE_INST(double)
+#endif
+#undef PIPE_INST
+
+}  // namespace pipe

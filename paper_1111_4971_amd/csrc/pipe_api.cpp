@@ -268,6 +268,13 @@ struct pipe_plan_s {
     int band_tile0 = 0;       // banded N = 0 x pass: packed-column tile, chosen by timing
     int band_pad = PIPE_BAND_PAD;   // banded: row pitch of the packed array = ceil(nz/2) + band_pad
     int a1pad = 0;                  // row pitch of A1 = lz/2 + a1pad (set with the launch schedule)
+    // sine-mode plans (modal.hip): the lattice axes, their matrices (one allocation)
+    // and the z pair table (in `table`); the padded-transform members above are
+    // then the default ones, used for the reported sizes alone
+    bool modal = false;
+    SineAxis sx{}, sy{};
+    int znh = 0;             // half length of the z convolution (zconv_length(nz))
+    void* frag = nullptr;
     double band_speedup = 0;  // banded build: measured 3-D solve time / banded solve time
     double* green = nullptr; // optional copy of Rbar
     double build_ms = 0;
@@ -297,6 +304,16 @@ int a1_pad_rule(const pipe_plan_s* p) {
     return ((p->nh & (p->nh - 1)) == 0 && row >= 8192) ? 16 : 0;
 }
 
+// z row pitch of the sine-mode arrays: nz rounded up to a 16-byte vector.
+int modal_nzp(const pipe_plan_s* p) {
+    const int v = 16 / p->rb;
+    return (p->nz + v - 1) / v * v;
+}
+
+// Workspace of a solve.  A sine-mode plan uses the two arrays (nmx, ny, nzp) and
+// (nmx, nmy, nzp), which always fit (at most 2 nx ny (nz + 3) reals against
+// 6 nx ny nz); it reports the padded transform's size all the same, so that which
+// meshes the fixed scratch accepts does not depend on the algorithm.
 size_t plan_ws_bytes(const pipe_plan_s* p) {
     const size_t cb = 2 * (size_t)p->rb;
     if (p->band >= 0) return 2 * align256((size_t)p->nx * p->ly * band_pitch(p) * cb);   // A, B: packed pairs
@@ -312,6 +329,14 @@ void plan_pass_bytes(const pipe_plan_s* p, double out[5]) {
     const double a2 = (double)p->nx * p->ly * p->nh * cb;
     const double orbits = (double)(p->lx / 2 + 1) * (p->ly / 2 + 1);
     const double tab = p->nval * orbits * (p->nh + 1) * rb;   // values read once per solve
+    if (p->modal) {
+        // x sines, y sines, z convolution (lines in place + pair table), y sines, x sines
+        const double b1 = (double)p->sx.nm * p->ny * p->nz * rb, b2 = (double)p->sx.nm * p->sy.nm * p->nz * rb;
+        out[0] = out[4] = phys + b1;
+        out[1] = out[3] = b1 + b2;
+        out[2] = 2.0 * b2 + (double)p->table_elems * rb;
+        return;
+    }
     if (p->band >= 0) {
         // banded: y forward (real in), x + banded product, y inverse (real out)
         const double A = (double)p->nx * p->ly * ((p->nz + 1) / 2) * cb;
@@ -410,20 +435,16 @@ pipe_status_t build_free_spectra(pipe_plan_s* p, hipStream_t st) {
     return PIPE_OK;
 }
 
-pipe_status_t build_spectra(pipe_plan_s* p, hipStream_t st, bool keep_green) {
-    if ((p->kind & 0x0f) == PIPE_GREEN_FREE) return build_free_spectra(p, st);
-    // Rbar rows: nx differences then 2nx - 1 sums along x, likewise along y
+// Rbar (3nx - 1, 3ny - 1, nz) into scratch memory: rows are the nx differences,
+// then the 2nx - 1 sums along x, likewise along y.
+pipe_status_t eval_green_table(pipe_plan_s* p, hipStream_t st, Scratch& s, double** rbar_out) {
     const int px = 3 * p->nx - 1, qy = 3 * p->ny - 1, rz = p->nz;
-    const int lx = p->lx, ly = p->ly, lz = p->lz, nh = p->nh;
-    Scratch s;
-    double *cx, *cy, *d, *u, *rbar, *buf;
+    double *cx, *cy, *d, *u, *rbar;
     HIP_TRY(s.get((void**)&cx, sizeof(double) * px * p->mx), "allocation (cos table)");
     HIP_TRY(s.get((void**)&cy, sizeof(double) * qy * p->my), "allocation (cos table)");
     HIP_TRY(s.get((void**)&d, sizeof(double) * (size_t)p->mx * p->my * rz), "allocation (mode table)");
     HIP_TRY(s.get((void**)&u, sizeof(double) * (size_t)p->mx * qy * rz), "allocation (partial sums)");
     HIP_TRY(s.get((void**)&rbar, sizeof(double) * (size_t)px * qy * rz), "allocation (Green table)");
-    HIP_TRY(s.get((void**)&buf, sizeof(double) * (size_t)lx * ly * lz), "allocation (spectrum buffer)");
-
     const double norm = 1.0 / (2.0 * M_PI * p->a * p->b);
     HIP_TRY(launch_cos_table(cx, p->nx, 2 * p->nx - 1, p->mx, p->hx / p->a, 2.0 * p->x0 / p->a, st), "cos table");
     HIP_TRY(launch_cos_table(cy, p->ny, 2 * p->ny - 1, p->my, p->hy / p->b, 2.0 * p->y0 / p->b, st), "cos table");
@@ -434,6 +455,25 @@ pipe_status_t build_spectra(pipe_plan_s* p, hipStream_t st, bool keep_green) {
     // Rbar (px x qy*rz) = Cx (px x mx) * U (mx x qy*rz)
     HIP_TRY(launch_gemm_f64(cx, u, rbar, px, qy * rz, p->mx, p->mx, (long)qy * rz, (long)qy * rz, 0, 0, 0, 1, st),
             "mode contraction (x)");
+    *rbar_out = rbar;
+    return PIPE_OK;
+}
+
+pipe_status_t keep_green_table(pipe_plan_s* p, const double* rbar, hipStream_t st) {
+    const size_t bytes = sizeof(double) * (size_t)(3 * p->nx - 1) * (3 * p->ny - 1) * p->nz;
+    HIP_TRY(dev_alloc((void**)&p->green, bytes), "allocation (kept Green table)");
+    HIP_TRY(hipMemcpyAsync(p->green, rbar, bytes, hipMemcpyDeviceToDevice, st), "Green table copy");
+    return PIPE_OK;
+}
+
+pipe_status_t build_spectra(pipe_plan_s* p, hipStream_t st, bool keep_green) {
+    if ((p->kind & 0x0f) == PIPE_GREEN_FREE) return build_free_spectra(p, st);
+    const int lx = p->lx, ly = p->ly, lz = p->lz, nh = p->nh;
+    Scratch s;
+    double *rbar, *buf;
+    pipe_status_t rs = eval_green_table(p, st, s, &rbar);
+    if (rs != PIPE_OK) return rs;
+    HIP_TRY(s.get((void**)&buf, sizeof(double) * (size_t)lx * ly * lz), "allocation (spectrum buffer)");
     for (int term = 0; term < 4; ++term) {
         const int xcorr = (term == 2 || term == 3), ycorr = (term == 1 || term == 3);
         HIP_TRY(launch_arrange(buf, rbar, p->nx, p->ny, p->nz, lx, ly, lz, xcorr, ycorr, st), "Green arrangement");
@@ -446,10 +486,60 @@ pipe_status_t build_spectra(pipe_plan_s* p, hipStream_t st, bool keep_green) {
                 "spectra x transform");
         HIP_TRY(launch_compress(buf, p->table, p->nyq, p->rb, term, lx, ly, nh, p->tile, st), "spectra compression");
     }
+    if (keep_green && (rs = keep_green_table(p, rbar, st)) != PIPE_OK) return rs;
+    HIP_TRY(hipStreamSynchronize(st), "plan build");
+    return PIPE_OK;
+}
+
+// One axis as a pipe lattice: h = w/N with N = n + 1, or N = n (the last node on
+// the wall), no offset.  h within 4 units of rounding of w/N: the same distances
+// as the mode sines see them to their own rounding.
+bool lattice_axis(int n, double h, double w, double x0, int m, SineAxis* ax) {
+    if (x0 != 0.0) return false;
+    for (int N : {n + 1, n}) {
+        if (std::fabs(N * h - w) > 4 * 0x1p-53 * w) continue;
+        ax->n = n;
+        ax->na = N - 1;
+        ax->nm = std::min(m, N - 1);
+        return ax->na >= 1 && ax->na <= kSineMaxRows;
+    }
+    return false;
+}
+
+// Sine matrices and the z pair table of a sine-mode plan (p->sx, p->sy set).
+pipe_status_t build_modal(pipe_plan_s* p, hipStream_t st, bool keep_green) {
+    const size_t fx = sine_frag_elems(p->sx.na, p->sx.nm), fy = sine_frag_elems(p->sy.na, p->sy.nm);
+    HIP_TRY(dev_alloc(&p->frag, (fx + fy) * p->rb), "allocation (sine matrices)");
+    p->sx.frag = p->frag;
+    p->sy.frag = (char*)p->frag + fx * p->rb;
+    HIP_TRY(launch_sine_frag((void*)p->sx.frag, p->rb, p->sx.na, p->sx.nm, st), "sine matrices");
+    HIP_TRY(launch_sine_frag((void*)p->sy.frag, p->rb, p->sy.na, p->sy.nm, st), "sine matrices");
+    const int nh = p->znh = zconv_length(p->nz), np = nh / 2 + 1;
+    const long lines = (long)p->sx.nm * p->sy.nm;
+    p->table_elems = 2 * (size_t)np * lines;
+    p->nyq_elems = 0;
+    HIP_TRY(dev_alloc(&p->table, p->table_elems * p->rb), "allocation (Green spectra)");
+    Scratch s;
+    // sequences and their spectra (in place), at most 512 MB of lines at a time
+    const long chunk = std::min(lines, std::max(1L, (512L << 20) / (16L * nh)));
+    double* buf;
+    HIP_TRY(s.get((void**)&buf, sizeof(double) * 2 * (size_t)nh * chunk), "allocation (spectrum buffer)");
+    // 1/(2 pi a b) of Eq. 9, the 4 of the sine products, the cell volume
+    const double scale = 4.0 / (2.0 * M_PI * p->a * p->b) * p->hx * p->hy * p->hz;
+    for (long l0 = 0; l0 < lines; l0 += chunk) {
+        const long nl = std::min(chunk, lines - l0);
+        HIP_TRY(launch_modal_factors(buf, p->sx, p->sy, p->mx, p->my, p->nz, nh, p->a, p->b, p->hz,
+                                     (p->kind & 0x0f) == PIPE_GREEN_IGF_Z, scale, l0, nl, st),
+                "mode factors");
+        HIP_TRY(launch_z_r2c<double>(nh, buf, 2 * nh, 2 * nh, buf, nh, nl, p->ctx->tw, st), "spectra z transform");
+        HIP_TRY(launch_modal_table(buf, (char*)p->table + (size_t)l0 * np * 2 * p->rb, p->rb, nh, nl, st),
+                "spectra compression");
+    }
     if (keep_green) {
-        HIP_TRY(dev_alloc((void**)&p->green, sizeof(double) * (size_t)px * qy * rz), "allocation (kept Green table)");
-        HIP_TRY(hipMemcpyAsync(p->green, rbar, sizeof(double) * (size_t)px * qy * rz, hipMemcpyDeviceToDevice, st),
-                "Green table copy");
+        double* rbar;
+        pipe_status_t rs = eval_green_table(p, st, s, &rbar);
+        if (rs == PIPE_OK) rs = keep_green_table(p, rbar, st);
+        if (rs != PIPE_OK) return rs;
     }
     HIP_TRY(hipStreamSynchronize(st), "plan build");
     return PIPE_OK;
@@ -552,6 +642,7 @@ void plan_free(pipe_plan_s* p) {
     for (hipEvent_t e : p->tev) (void)hipEventSynchronize(e);
     for (hipEvent_t e : p->tev) (void)hipEventDestroy(e);
     if (p->table) (void)hipFree(p->table);
+    if (p->frag) (void)hipFree(p->frag);
     if (p->green) (void)hipFree(p->green);
     delete p;
 }
@@ -607,6 +698,52 @@ pipe_status_t run_passes(pipe_plan_s* p, const void* rho, void* phi, void* ws, h
     HIP_TRY(launch_z_c2r<real>(nh, A1, p1, (real*)phi, nz, nz, (long)nx * ny, scale, tw, st, nullptr, 1, true,
                                p->zcap),
             "z inverse pass");
+    if (ev) HIP_TRY(hipEventRecord(ev[5], st), "event");
+    return PIPE_OK;
+}
+
+// The five passes of a sine-mode plan (modal.hip), of one solve or of a group of
+// n solves (args: n descriptors per pass).  The
+// operator is symmetric, so the adjoint is the same.
+struct ModalLayout {
+    int nzp;
+    long p1, p2;      // x-mode strides of (nmx, ny, nzp) and (nmx, nmy, nzp)
+    size_t b2_off;    // byte offset of the second array
+};
+ModalLayout modal_layout(const pipe_plan_s* p) {
+    ModalLayout m;
+    m.nzp = modal_nzp(p);
+    m.p1 = (long)p->ny * m.nzp;
+    m.p2 = (long)p->sy.nm * m.nzp;
+    m.b2_off = align256((size_t)p->sx.nm * m.p1 * p->rb);
+    return m;
+}
+// Whether a user array's z rows may be accessed as 16-byte vectors.
+bool modal_vec(const pipe_plan_s* p, const void* q) { return ((uintptr_t)q % 16) == 0 && p->nz == modal_nzp(p); }
+
+template <typename real>
+pipe_status_t run_modal_passes(pipe_plan_s* p, const void* rho, void* phi, void* ws, bool vec_in, bool vec_out,
+                               hipStream_t st, hipEvent_t* ev, const GroupArgs* args = nullptr, int n = 1) {
+    const ModalLayout m = modal_layout(p);
+    const int ny = p->ny, nz = p->nz, nzp = m.nzp;
+    char* B1 = (char*)ws;
+    char* B2 = B1 + m.b2_off;
+    auto g = [&](int pass) { return args ? args + (size_t)pass * n : nullptr; };
+    if (ev) HIP_TRY(hipEventRecord(ev[0], st), "event");
+    HIP_TRY(launch_sine<real>(p->sx, false, rho, B1, nz, nzp, nz, (long)ny * nz, nzp, m.p1, ny, vec_in, st, g(0), n),
+            "x sine transform");
+    if (ev) HIP_TRY(hipEventRecord(ev[1], st), "event");
+    HIP_TRY(launch_sine<real>(p->sy, false, B1, B2, nz, nzp, m.p1, nzp, m.p2, nzp, p->sx.nm, true, st, g(1), n),
+            "y sine transform");
+    if (ev) HIP_TRY(hipEventRecord(ev[2], st), "event");
+    HIP_TRY(launch_zconv<real>(p->znh, B2, nzp, nz, (long)p->sx.nm * p->sy.nm, p->table, p->ctx->tw, st, g(2), n),
+            "z convolution");
+    if (ev) HIP_TRY(hipEventRecord(ev[3], st), "event");
+    HIP_TRY(launch_sine<real>(p->sy, true, B2, B1, nz, nzp, m.p2, nzp, m.p1, nzp, p->sx.nm, true, st, g(3), n),
+            "y sine transform back");
+    if (ev) HIP_TRY(hipEventRecord(ev[4], st), "event");
+    HIP_TRY(launch_sine<real>(p->sx, true, B1, phi, nz, nzp, nzp, m.p1, nz, (long)ny * nz, ny, vec_out, st, g(4), n),
+            "x sine transform back");
     if (ev) HIP_TRY(hipEventRecord(ev[5], st), "event");
     return PIPE_OK;
 }
@@ -738,7 +875,11 @@ pipe_status_t solve_impl(pipe_plan_t plan, const void* rho, void* phi, void* ws,
     if (plan->band >= 0)
         s = plan->rb == 8 ? run_band_passes<double>(plan, rho, phi, ws, st, adjoint, ev)
                           : run_band_passes<float>(plan, rho, phi, ws, st, adjoint, ev);
-    else
+    else if (plan->modal) {
+        const bool vi = modal_vec(plan, rho), vo = modal_vec(plan, phi);
+        s = plan->rb == 8 ? run_modal_passes<double>(plan, rho, phi, ws, vi, vo, st, ev)
+                          : run_modal_passes<float>(plan, rho, phi, ws, vi, vo, st, ev);
+    } else
         s = plan->rb == 8 ? run_passes<double>(plan, rho, phi, ws, st, adjoint, ev)
                           : run_passes<float>(plan, rho, phi, ws, st, adjoint, ev);
     if (s == PIPE_OK && record_use) {
@@ -1153,6 +1294,7 @@ pipe_status_t create_plan(int nx, int ny, int nz, double hx, double hy, double h
     const bool keep = (kind & PIPE_KEEP_GREEN) != 0;
     const bool tune = (kind & (PIPE_AUTOTUNE | PIPE_AUTOTUNE_BATCH)) != 0 && lx == 0 && ly == 0 && lz == 0;
     const int tune_members = (kind & PIPE_AUTOTUNE_BATCH) ? 16 : 1;
+    const bool own_lengths = lx == 0 && ly == 0 && lz == 0;
     kind &= 0xff;
     pipe_status_t s = validate(nx, ny, nz, hx, hy, hz, a, b, x0, y0, kind, mx, my, &lx, &ly, &lz, free_space);
     if (s != PIPE_OK) return s;
@@ -1183,6 +1325,27 @@ pipe_status_t create_plan(int nx, int ny, int nz, double hx, double hy, double h
     p->x0 = x0; p->y0 = y0; p->g0 = g0;
     p->device = dev; p->ctx = ctx;
     p->nval = free_space ? 1 : 9;
+    // Sine modes where the mesh fills the pipe's lattice in x and y and the caller
+    // left the algorithm open: explicit padded lengths or a forced schedule ask
+    // for the padded transform.
+    const char* sched = getenv("PIPE_SCHEDULE");
+    if (!free_space && own_lengths && (!sched || !strcmp(sched, "fixed")) && lattice_axis(nx, hx, a, x0, mx, &p->sx) &&
+        lattice_axis(ny, hy, b, y0, my, &p->sy)) {
+        p->modal = true;
+        p->tile = xprod_tile(lx, p->rb);
+        p->a1pad = a1_pad_rule(p);
+        s = build_modal(p, (hipStream_t)hip_stream, keep);
+        if (s != PIPE_OK) {
+            plan_free(p);
+            return s;
+        }
+        p->ws_bytes = plan_ws_bytes(p);
+        p->tune_ms = tune_ms;
+        p->build_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+        reg_add(p);
+        *out = p;
+        return PIPE_OK;
+    }
     const size_t orbits = (size_t)(lx / 2 + 1) * (ly / 2 + 1);
     // launch schedule (kz tile, row pitch, z block cap); the table layout follows the tile
     s = tune_schedule(p, tune_members, (hipStream_t)hip_stream);
@@ -1412,11 +1575,12 @@ pipe_status_t pipe_plan_info(pipe_plan_t p, pipe_plan_info_t* out) {
     out->tune_ms = p->tune_ms;
     out->band = p->band;
     out->band_speedup = p->band_speedup;
-    out->xtile = p->band >= 0 ? (p->band == 0 ? p->band_tile0 : 0) : p->tile;
-    out->apad = p->band >= 0 ? 0 : p->apad;
-    out->zblocks = p->band >= 0 ? 0 : p->zcap;
-    out->xnt = p->band >= 0 ? 0 : p->xnt;
-    out->a1pad = p->band >= 0 ? 0 : p->a1pad;
+    const bool padded = p->band < 0 && !p->modal;   // the schedule belongs to the padded transform
+    out->xtile = p->band == 0 ? p->band_tile0 : padded ? p->tile : 0;
+    out->apad = padded ? p->apad : 0;
+    out->zblocks = padded ? p->zcap : 0;
+    out->xnt = padded ? p->xnt : 0;
+    out->a1pad = padded ? p->a1pad : 0;
     return PIPE_OK;
 }
 
@@ -1516,11 +1680,30 @@ pipe_status_t pipe_plan_spectra(pipe_plan_t p, void* out, void* stream) {
     if (!reg_has(p)) return fail(PIPE_ERR_INVALID_ARG, "invalid or destroyed plan handle");
     if (!out) return fail(PIPE_ERR_INVALID_ARG, "out must be non-null");
     hipStream_t st = (hipStream_t)stream;
-    if (p->band >= 0)
+    if (p->band >= 0) {
         HIP_TRY(hipMemcpyAsync(out, p->table, p->table_elems * p->rb, hipMemcpyDeviceToDevice, st), "spectra copy");
-    else
+    } else if (p->modal) {
+        // the padded transform's spectra, built for this call
+        pipe_plan_s q;
+        q.nx = p->nx; q.ny = p->ny; q.nz = p->nz; q.lx = p->lx; q.ly = p->ly; q.lz = p->lz; q.nh = p->nh;
+        q.mx = p->mx; q.my = p->my; q.kind = p->kind; q.rb = p->rb;
+        q.hx = p->hx; q.hy = p->hy; q.hz = p->hz; q.a = p->a; q.b = p->b; q.x0 = p->x0; q.y0 = p->y0;
+        q.device = p->device; q.ctx = p->ctx; q.tile = p->tile;
+        const size_t orbits = (size_t)(q.lx / 2 + 1) * (q.ly / 2 + 1);
+        q.table_elems = q.nval * orbits * ((q.nh + q.tile - 1) / q.tile) * q.tile;
+        q.nyq_elems = q.nval * orbits;
+        Scratch s;
+        HIP_TRY(s.get(&q.table, (q.table_elems + q.nyq_elems) * q.rb), "allocation (Green spectra)");
+        q.nyq = (char*)q.table + q.table_elems * q.rb;
+        HIP_TRY(hipMemsetAsync(q.table, 0, (q.table_elems + q.nyq_elems) * q.rb, st), "spectra clear");
+        pipe_status_t rs = build_spectra(&q, st, false);
+        if (rs != PIPE_OK) return rs;
+        HIP_TRY(launch_untile(q.table, q.nyq, out, q.rb, q.lx, q.ly, q.nh, q.tile, st, q.nval), "spectra copy");
+        HIP_TRY(hipStreamSynchronize(st), "spectra copy");
+    } else {
         HIP_TRY(launch_untile(p->table, p->nyq, out, p->rb, p->lx, p->ly, p->nh, p->tile, st, p->nval),
                 "spectra copy");
+    }
     HIP_TRY(hipStreamSynchronize(st), "spectra copy");
     return PIPE_OK;
 }
@@ -1654,6 +1837,7 @@ template <typename real>
 // shared_table: every member solves on the same plan (many charges, one spectra table).
 pipe_status_t launch_group(pipe_plan_s* p, const GroupArgs* args, int n, bool al_in, bool al_out, hipStream_t st,
                            bool shared_table) {
+    if (p->modal) return run_modal_passes<real>(p, nullptr, nullptr, nullptr, al_in, al_out, st, nullptr, args, n);
     const int nx = p->nx, ny = p->ny, nz = p->nz, ly = p->ly, nh = p->nh;
     const TwiddleBank& tw = p->ctx->tw;
     const real scale = (real)0;  // taken from each member's GroupArgs
@@ -1699,7 +1883,10 @@ pipe_status_t pipe_batch_create(const pipe_plan_t* plans, int count, pipe_batch_
             pipe_plan_s* r = b->groups[k].rep;
             if (!b->groups[k].banded && r->nx == p->nx && r->ny == p->ny && r->nz == p->nz && r->lx == p->lx &&
                 r->ly == p->ly && r->lz == p->lz && r->nval == p->nval && r->tile == p->tile &&
-                r->apad == p->apad && r->zcap == p->zcap && r->xnt == p->xnt && r->a1pad == p->a1pad)
+                r->apad == p->apad && r->zcap == p->zcap && r->xnt == p->xnt && r->a1pad == p->a1pad &&
+                r->modal == p->modal &&
+                (!p->modal || (r->sx.na == p->sx.na && r->sx.nm == p->sx.nm && r->sy.na == p->sy.na &&
+                               r->sy.nm == p->sy.nm)))   // the same sine matrices
                 g = (int)k;
         }
         if (g < 0) {
@@ -1784,8 +1971,8 @@ pipe_status_t pipe_batch_solve(pipe_batch_t b, const void* const* rho, void* con
             const size_t m = g.members.size();
             bool al_in = true, al_out = true;
             for (int i : g.members) {
-                al_in = al_in && ((uintptr_t)rho[i] % (2 * b->rb) == 0);
-                al_out = al_out && ((uintptr_t)phi[i] % (2 * b->rb) == 0);
+                al_in = al_in && (g.rep->modal ? modal_vec(g.rep, rho[i]) : (uintptr_t)rho[i] % (2 * b->rb) == 0);
+                al_out = al_out && (g.rep->modal ? modal_vec(g.rep, phi[i]) : (uintptr_t)phi[i] % (2 * b->rb) == 0);
             }
             flags.push_back((char)(al_in | (al_out << 1)));
             if (g.banded) {   // launched directly with its own pointers
@@ -1800,6 +1987,15 @@ pipe_status_t pipe_batch_solve(pipe_batch_t b, const void* const* rho, void* con
                 const int i = g.members[k];
                 pipe_plan_s* p = b->plans[i];
                 char* A1 = (char*)ws + b->ws_off[i];
+                if (p->modal) {
+                    char* B2 = A1 + modal_layout(p).b2_off;
+                    a[0 * m + k] = {rho[i], A1, nullptr, nullptr, 0.0};
+                    a[1 * m + k] = {A1, B2, nullptr, nullptr, 0.0};
+                    a[2 * m + k] = {B2, B2, p->table, nullptr, 0.0};
+                    a[3 * m + k] = {B2, A1, nullptr, nullptr, 0.0};
+                    a[4 * m + k] = {A1, phi[i], nullptr, nullptr, 0.0};
+                    continue;
+                }
                 char* A2 = A1 + align256((size_t)p->nx * p->ny * a1_pitch(p) * 2 * p->rb);
                 const double scale = p->hx * p->hy * p->hz / ((double)p->lx * p->ly * p->lz);
                 a[0 * m + k] = {rho[i], A1, nullptr, nullptr, 0.0};

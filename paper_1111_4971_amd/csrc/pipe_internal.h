@@ -179,6 +179,66 @@ hipError_t launch_compress_band(const void* spec, double* tmp, int term, int lx,
 hipError_t launch_band_coefficients(const double* tmp, void* table, int real_bytes, int lx, int ly, int D,
                                     hipStream_t st);
 
+// Sine-mode path (modal.hip).  One axis of a mesh that fills the pipe's lattice:
+// node i at (i + 1) a/N, i < na = N - 1 (na = n, or n - 1 with node n - 1 on the
+// wall); modes m' = 1 .. nm kept, stored odd ones first.  frag: the sine matrices
+// as matrix-core operands (plan precision), forward then inverse.
+constexpr int kSineMaxRows = 512;
+struct SineAxis {
+    int n, na, nm;
+    const void* frag;
+};
+inline size_t sine_frag_elems(int na, int nm, bool both = true) {
+    const size_t th = ((na + 1) / 2 + 15) / 16, tm = ((nm + 1) / 2 + 15) / 16;
+    return (both ? 2 : 1) * 2 * th * tm * 256;
+}
+struct SineArgs {
+    const void* in;
+    void* out;
+    const void* frag;
+    long in_ss, in_es, out_ss, out_es;   // slab and row strides (reals)
+    long ngroups;                        // vector columns of all slabs
+    int wv;                              // vector columns per slab
+    int nz;                              // values per z row (columns beyond are padding)
+    int n, na, h, he, no, ne;            // rows, lattice rows, half sizes of rows and modes
+    int rt, kb, g;                       // 16-row tiles, 16-deep blocks, 16-lane column groups per block
+};
+// Sine transform along one axis of (slab, row, z) arrays: forward na rows ->
+// nm modes, inverse nm modes -> n rows (a wall row is written as zeros).
+// in/out address z rows of nz (user arrays) or nzp (a multiple of a 16-byte
+// vector) values.  user_vec: the input of a forward, the output of an inverse
+// transform may be accessed as 16-byte vectors (rows aligned and of nzp values);
+// the other side always is.
+template <typename real>
+hipError_t launch_sine(const SineAxis& ax, bool inverse, const void* in, void* out, int nz, int nzp, long in_ss,
+                       long in_es, long out_ss, long out_es, long nslabs, bool user_vec, hipStream_t s,
+                       const GroupArgs* group = nullptr, int ngroup = 1);
+// Half lengths of the z convolution: those whose line lies inside one wavefront
+// (must match PIPE_FOR_EACH_ZCONV_N).
+constexpr int kZconvLengths[] = {8, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
+inline int zconv_length(int n) {
+    for (int v : kZconvLengths)
+        if (v >= n) return v;
+    return -1;
+}
+// z convolution in place: nlines lines of n <= nh values, pitch (even) apart,
+// with the pair table of launch_modal_table (nh/2 + 1 pairs per line).
+// group entries: out = the lines, table.
+template <typename real>
+hipError_t launch_zconv(int nh, void* data, long pitch, int n, long nlines, const void* table, const TwiddleBank& tw,
+                        hipStream_t s, const GroupArgs* group = nullptr, int ngroup = 1);
+// Sine matrices of one axis into frag (green.hip).
+hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStream_t st);
+// Folded z factors of mode lines [line0, line0 + nlines) (line = x mode * nmy + y
+// mode, odd modes first) as even sequences of length 2 nh: out[line - line0][s].
+// W(r) = scale sum over the folded modes (m, n), m <= mx, n <= my, of
+// g(kappa_mn, r hz)/kappa_mn for r < rz, 0 beyond.
+hipError_t launch_modal_factors(double* out, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz, int nh,
+                                double a, double b, double hz, int igf, double scale, long line0, long nlines,
+                                hipStream_t st);
+// Pair table rows from the packed spectra of those sequences (nlines x nh complex).
+hipError_t launch_modal_table(const void* spec, void* table, int real_bytes, int nh, long nlines, hipStream_t st);
+
 // Batched contiguous complex lines (fft3d.hip): nlines lines of length n at
 // in + l n, out + l n (in == out allowed), forward (W^{jk}) or inverse (W^{-jk}),
 // unscaled.

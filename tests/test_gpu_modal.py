@@ -1,0 +1,156 @@
+"""Solves in the sine modes of the cross-section (meshes that fill the pipe's
+lattice, lengths left to the library) against the literal Eq. 10 oracle and
+against the padded transform of the same mesh (explicit padded lengths), at the
+edges of the kernels' tiles, over the geometries that take or leave the route,
+and through every other way to run a plan.
+"""
+import numpy as np
+import pytest
+
+from helpers import TOL, gpu_solve, log, oracle_input, rel_l2, rel_max
+
+pytestmark = pytest.mark.gpu
+
+A, B, HZ = 1.2, 0.9, 0.05
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
+def _plan(shape, prec, wall=(False, False), modes=None, kind=1, padded=False, **kw):
+    from paper_1111_4971_amd import pipe
+    nx, ny, nz = shape
+    hx, hy = A / (nx if wall[0] else nx + 1), B / (ny if wall[1] else ny + 1)
+    mx, my = modes or (2 * nx + 1, 2 * ny)
+    L = pipe.default_lengths(nx, ny, nz, prec) if padded else None
+    plan = pipe.GreenPlan(nx, ny, nz, hx, hy, HZ, A, B, kind=kind, precision=prec, mx=mx, my=my, L=L, **kw)
+    assert (plan.info.xtile == 0) == (not padded)
+    return plan, (hx, hy, HZ, A, B, mx, my, kind)
+
+
+def _rho(shape):
+    return np.random.default_rng(sum(shape)).standard_normal(shape)
+
+
+# rows at the edges of 16-row tiles and of the folded halves, register depths 1..8
+# (up to 256 rows), the streamed depths beyond, one and two nodes
+EDGES = [1, 2, 3, 15, 16, 17, 31, 32, 33, 34, 64, 65, 95, 97, 128, 129, 161, 193, 225, 255, 256, 257, 300, 511, 512]
+
+
+@pytest.mark.parametrize("n", EDGES)
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_every_tile_edge_matches_eq10_oracle(torch_cuda, n, prec):
+    from oracle import fourterm
+    for shape, wall in (((n, 2, 5), (False, False)), ((3, n, 4), (False, n > 1))):
+        log("sine modes %s %s wall=%s" % (prec, shape, wall))
+        plan, g = _plan(shape, prec, wall)
+        rho = _rho(shape)
+        got = gpu_solve(plan, rho)
+        ref = fourterm.solve(oracle_input(rho, prec), *g)
+        assert rel_l2(got, ref) <= TOL[prec] and rel_max(got, ref) <= TOL[prec], (shape, rel_l2(got, ref))
+        plan.close()
+
+
+# z lengths at and around the transform lengths, odd and even, unpadded rows and not
+@pytest.mark.parametrize("nz", [1, 2, 3, 7, 8, 9, 16, 17, 24, 31, 33, 48, 63, 65, 96, 100, 128, 129, 190, 193, 256,
+                                257, 384, 400, 512, 600, 769, 1024])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_every_z_length_matches_eq10_oracle(torch_cuda, nz, prec):
+    from oracle import fourterm
+    shape = (5, 4, nz)
+    log("sine modes %s nz=%d" % (prec, nz))
+    plan, g = _plan(shape, prec)
+    rho = _rho(shape)
+    got = gpu_solve(plan, rho)
+    ref = fourterm.solve(oracle_input(rho, prec), *g)
+    assert rel_l2(got, ref) <= TOL[prec] and rel_max(got, ref) <= TOL[prec], rel_l2(got, ref)
+
+
+# few modes (rectangular transforms), modes that fold once and several times
+@pytest.mark.parametrize("modes", [(1, 1), (3, 40), (20, 20), (39, 30), (40, 31), (200, 155)])
+@pytest.mark.parametrize("kind", [0, 1])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_mode_counts_match_the_padded_transform(torch_cuda, modes, kind, prec):
+    shape = (39, 31, 22)
+    rho = _rho(shape)
+    for wall in ((False, False), (True, True)):
+        log("sine modes %s modes=%s kind=%d wall=%s" % (prec, modes, kind, wall))
+        p, _ = _plan(shape, prec, wall, modes, kind)
+        q, _ = _plan(shape, prec, wall, modes, kind, padded=True)
+        got, ref = gpu_solve(p, rho), gpu_solve(q, rho)
+        assert rel_l2(got, ref) <= 2 * TOL[prec] and rel_max(got, ref) <= 2 * TOL[prec]
+        x = torch_cuda.from_numpy(rho).to("cuda", p.dtype)
+        assert rel_l2(p.adjoint(x).double().cpu(), ref) <= 2 * TOL[prec]
+        # the padded transform's spectra are still there to be read
+        for s, t in zip(p.spectra(), q.spectra()):
+            assert torch_cuda.equal(s, t)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_route_follows_the_geometry(torch_cuda, prec):
+    """Off the lattice (spacing, offset) or with lengths of its own a mesh keeps the
+    padded transform; a spacing within rounding of the lattice takes the modes."""
+    from paper_1111_4971_amd import pipe
+    mk = lambda hx, hy, **kw: pipe.GreenPlan(11, 9, 10, hx, hy, HZ, A, B, precision=prec, **kw)
+    hx, hy = A / 12, B / 10
+    for plan, modal in ((mk(hx, hy), True), (mk(np.nextafter(hx, 0), hy), True), (mk(hx * (1 - 1e-12), hy), False),
+                        (mk(hx, 0.9 * hy), False), (mk(A / 11, B / 9), True), (mk(A / 13, hy), False),
+                        (mk(A / 24, hy, offset=(A / 24, 0.0)), False), (mk(hx, hy, L=(0, 0, 24)), False),
+                        (mk(hx, hy, band=2), None)):
+        if modal is not None:
+            assert (plan.info.xtile == 0) == modal, (plan.info.hx, plan.info.hy)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("shape", [(20, 17, 24), (33, 18, 37)])
+def test_buffers_batches_and_graphs_agree(torch_cuda, prec, shape):
+    """The same bits from unaligned arrays, the fixed scratch, batches (alone, one plan
+    several times, beside padded and banded plans, unaligned members) and replays of a
+    captured solve with other work between them."""
+    torch = torch_cuda
+    from paper_1111_4971_amd import pipe
+    plan, _ = _plan(shape, prec)
+    other, _ = _plan(shape, prec, modes=(50, 50))
+    padded, _ = _plan(shape, prec, padded=True)
+    banded = pipe.GreenPlan(*shape, A / (shape[0] + 1), B / (shape[1] + 1), HZ, A, B, precision=prec, band=1)
+    n = int(np.prod(shape))
+    x = torch.from_numpy(_rho(shape)).to("cuda", plan.dtype)
+    ref = plan.solve(x)
+
+    def odd(t):     # the same values one element off a vector boundary
+        big = torch.zeros(n + 1, device="cuda", dtype=plan.dtype)
+        v = big[1:].view(shape)
+        v.copy_(t)
+        return v
+
+    log("sine modes %s %s: unaligned, scratch" % (prec, shape))
+    xo, out = odd(x), odd(x)
+    assert torch.equal(plan.solve(xo, out=out), ref) and torch.equal(plan.solve(xo), ref)
+    assert torch.equal(plan.solve(x, out=out), ref)
+    assert torch.equal(plan.solve_noalloc(x, torch.empty_like(x)), ref)
+    log("sine modes %s %s: batch" % (prec, shape))
+    plans = [plan, padded, plan, banded, other, plan]
+    rhos = [x, x, 2 * x, x, x, xo]
+    b = pipe.Batch(plans)
+    for ins in (rhos, [x] * 6, rhos):
+        outs = [torch.empty_like(x) for _ in plans]
+        b.solve(ins, outs)
+        for p, r, o in zip(plans, ins, outs):
+            assert torch.equal(o, p.solve(r))
+    log("sine modes %s %s: captured solve" % (prec, shape))
+    y, ws, s = torch.empty_like(x), plan.workspace(), torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(g, stream=s):
+        plan.solve(x, out=y, workspace=ws, stream=s)
+    for k in range(3):
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, ref)
+        plan.solve(k * x, workspace=ws)
+        torch.cuda.synchronize()
