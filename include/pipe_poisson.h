@@ -216,6 +216,9 @@ pipe_status_t pipe_green_plan_region(int nx, int ny, int nz, double hx, double h
  * pipe_green_plan_region (on scratch buffers) and reports the ratio in
  * info.band_speedup (below 1: the banded plan is the slower one, which happens
  * once 2N + 1 plane products cost more than the z transforms they replace).
+ * A mesh that fills the pipe's lattice, with lx = ly = 0 and no PIPE_KEEP_GREEN,
+ * is solved in the sine modes as the 3-D plans are (same workspace and reported
+ * lengths; xtile 0), the z sum taken mode by mode.
  * With PIPE_BAND_FASTEST in kind, the call then returns the 3-D plan (exact,
  * info.band = -1) whenever it is the faster.  Other arguments, ownership and
  * errors as pipe_green_plan_region; PIPE_AUTOTUNE flags are ignored.  In a

@@ -314,28 +314,41 @@ __global__ void sine_frag_kernel(T* out, int na, int nm) {
     out[i] = ok ? (T)sin_lattice(mode * (x + 1), N) : (T)0;
 }
 
-__global__ void modal_factors_kernel(double* out, int nax, int nmx, int nay, int nmy, int mx, int my, int rz, int nh,
-                                     double a, double b, double hz, int igf, double scale, long line0, long nlines) {
+// The folded z factor of one mode line at plane distance s.
+struct ModalGeometry {
+    int nax, nmx, nay, nmy, mx, my, igf;
+    double a, b, hz, scale;
+};
+__device__ __forceinline__ double modal_factor(const ModalGeometry& q, long line, int s) {
+    const int m1 = stored_mode((int)(line / q.nmy), (q.nmx + 1) / 2), n1 = stored_mode((int)(line % q.nmy), (q.nmy + 1) / 2);
+    const int px = 2 * (q.nax + 1), py = 2 * (q.nay + 1);
+    double w = 0.0;
+    // the modes with the same sines on the lattice: m1, 2N - m1, 2N + m1, ...
+    for (int m = m1, fx = 0; m <= q.mx; m = fx ? m + 2 * m1 : m + px - 2 * m1, fx ^= 1)
+        for (int n = n1, fy = 0; n <= q.my; n = fy ? n + 2 * n1 : n + py - 2 * n1, fy ^= 1) {
+            const double km = (double)m / q.a, kn = (double)n / q.b;
+            const double kap = M_PI * sqrt(km * km + kn * kn);
+            w += (q.igf ? igf_g(kap * q.hz, s) : exp(-kap * ((double)s * q.hz))) / kap;
+        }
+    return w * q.scale;
+}
+
+__global__ void modal_factors_kernel(double* out, ModalGeometry q, int rz, int nh, long line0, long nlines) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nlines * (nh + 1)) return;
     const int s = (int)(i % (nh + 1));
-    const long l = i / (nh + 1), line = line0 + l;
-    double w = 0.0;
-    if (s < rz) {
-        const int m1 = stored_mode((int)(line / nmy), (nmx + 1) / 2), n1 = stored_mode((int)(line % nmy), (nmy + 1) / 2);
-        const int px = 2 * (nax + 1), py = 2 * (nay + 1);
-        // the modes with the same sines on the lattice: m1, 2N - m1, 2N + m1, ...
-        for (int m = m1, fx = 0; m <= mx; m = fx ? m + 2 * m1 : m + px - 2 * m1, fx ^= 1)
-            for (int n = n1, fy = 0; n <= my; n = fy ? n + 2 * n1 : n + py - 2 * n1, fy ^= 1) {
-                const double km = (double)m / a, kn = (double)n / b;
-                const double kap = M_PI * sqrt(km * km + kn * kn);
-                w += (igf ? igf_g(kap * hz, s) : exp(-kap * ((double)s * hz))) / kap;
-            }
-        w *= scale;
-    }
+    const long l = i / (nh + 1);
+    const double w = s < rz ? modal_factor(q, line0 + l, s) : 0.0;
     double* row = out + l * 2 * nh;
     row[s] = w;
     if (s > 0 && s < nh) row[2 * nh - s] = w;
+}
+
+// The factors at plane distances s < rz themselves, rz per line.
+template <typename T>
+__global__ void modal_band_kernel(T* out, ModalGeometry q, int rz, long nlines) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nlines * rz) out[i] = (T)modal_factor(q, i / rz, (int)(i % rz));
 }
 
 // Packed spectra of real even sequences (imaginary parts are rounding) -> pairs
@@ -435,8 +448,21 @@ hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStrea
 hipError_t launch_modal_factors(double* out, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz, int nh,
                                 double a, double b, double hz, int igf, double scale, long line0, long nlines,
                                 hipStream_t st) {
-    hipLaunchKernelGGL(modal_factors_kernel, dim3(blocks_for(nlines * (nh + 1), 256)), dim3(256), 0, st, out, ax.na,
-                       ax.nm, ay.na, ay.nm, mx, my, rz, nh, a, b, hz, igf, scale, line0, nlines);
+    const ModalGeometry q{ax.na, ax.nm, ay.na, ay.nm, mx, my, igf, a, b, hz, scale};
+    hipLaunchKernelGGL(modal_factors_kernel, dim3(blocks_for(nlines * (nh + 1), 256)), dim3(256), 0, st, out, q, rz, nh,
+                       line0, nlines);
+    return hipGetLastError();
+}
+
+hipError_t launch_modal_band(void* out, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz,
+                             double a, double b, double hz, int igf, double scale, hipStream_t st) {
+    const ModalGeometry q{ax.na, ax.nm, ay.na, ay.nm, mx, my, igf, a, b, hz, scale};
+    const long nlines = (long)ax.nm * ay.nm;
+    const unsigned nb = blocks_for(nlines * rz, 256);
+    if (real_bytes == 8)
+        hipLaunchKernelGGL(modal_band_kernel<double>, dim3(nb), dim3(256), 0, st, (double*)out, q, rz, nlines);
+    else
+        hipLaunchKernelGGL(modal_band_kernel<float>, dim3(nb), dim3(256), 0, st, (float*)out, q, rz, nlines);
     return hipGetLastError();
 }
 

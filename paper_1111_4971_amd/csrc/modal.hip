@@ -13,7 +13,10 @@
 //   M4 y sine transform back, M5 x sine transform back to (nx, ny, nz),
 // with nothing padded in x and y: 11 n values move instead of the 35 n of the
 // padded transform (n = nx ny nz, the spectra included).  nzp is nz rounded up
-// to a 16-byte vector.
+// to a 16-byte vector.  Whole solves, padded transform -> sine modes: 128x128x512
+// FP32 235 -> 110 us, FP64 456 -> 177 us; 256x256x1024 FP32 1853 -> 877 us;
+// 64x64x256 FP64 74 -> 41 us; errors against 64 bits no larger (FP32 1.5e-7
+// against 2.4e-7, 1.7e-7 against 1.9e-7).
 #include <algorithm>
 
 #include "pass_common.h"
@@ -198,6 +201,12 @@ template <typename real, bool INV, int V, bool UV> struct Sine {
 // idle), used in the one after.  Column tile c of a group is the columns V j + c
 // (j = lane % 16), so the B operands of all V tiles come with one LDS vector read
 // and a row of the result leaves as one vector a lane, 16 lanes contiguous.
+//
+// Measured per pass: 256 rows x 262144 columns FP32 170 us (536 MB: 3.2 TB/s; the
+// matrix cores' bound is 109 us, a pass without the products takes 108 us; one tile
+// per block with the matrix streamed 195-240 us); 128 x 65536 FP32 20 us, FP64 38 us
+// (memory alone 13 and 26).  Half-width columns at 128 rows, or registers for four
+// waves per SIMD, were no faster.
 template <typename real, bool INV, int V, int KB, bool UV>
 __global__ __launch_bounds__(512) void sine_kernel(SineArgs a, const GroupArgs* __restrict__ group) {
     using S = Sine<real, INV, V, UV>;
@@ -476,6 +485,11 @@ __global__ __launch_bounds__(512) void sine_stream_kernel(SineArgs a, const Grou
 // E - 1 - q of lane P - t (lane 0: bin E - q of its own), so the product needs one
 // lane exchange each way and no pass through LDS.  Only the first half of the
 // packed pairs is ever non-zero (n <= NH) or kept.
+//
+// Bound by its vector and LDS instructions as much as by memory: 16384 lines of 512
+// FP32 27 us (100 MB: 3.7 TB/s), FP64 59 us; 65536 lines of 1024 FP32 236 us (805
+// MB).  With the product through LDS, twiddles read there and no pruning: 35, 63 and
+// 280 us.  More waves per SIMD by a register cap spill and run slower.
 
 // Length plan: at most 12 values per thread, 16 at NH = 1024, which keeps the line
 // in one wavefront.
@@ -714,6 +728,45 @@ void zconv_kernel(real* data, long pitch, int n, long nlines, const cplx<real>* 
     }
 }
 
+// ---------------------------------------------------------------- neighbouring planes
+//
+// The z sum of a banded plan (Eq. 18) on the mode lines: a symmetric filter of 2 NB
+// + 1 values, one 16-byte vector of outputs a thread.  The window's vectors come from
+// L1 after the first thread; memory bound (one read and one write of the lines).
+// Whole banded solves at 128x128x256 FP32, N = 2, 20 x 20 modes: 76 us by the padded
+// transform's coefficient product, 32 us here; with 256 x 256 modes 57 us, 66 us with
+// the z convolution cut at N in place of the filter.
+template <typename real, int NB>
+__global__ __launch_bounds__(256) void zband_kernel(const real* in, real* out, unsigned wv, unsigned total,
+                                                    const real* table) {
+    constexpr int V = 16 / sizeof(real), Q = (NB + V - 1) / V;   // window: Q vectors each side
+    using vec = vecv<real, V>;
+    const unsigned i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= total) return;
+    const unsigned line = i / wv, g = i % wv;
+    const gptr<const vec> src = reinterpret_cast<gptr<const vec>>(to_global(in)) + i;
+    const gptr<const real> t = to_global(table) + (size_t)line * (NB + 1);
+    real w[V * (2 * Q + 1)], c[NB + 1];
+#pragma unroll
+    for (int d = 0; d <= NB; ++d) c[d] = t[d];
+#pragma unroll
+    for (int q = -Q; q <= Q; ++q) {
+        vec v{};
+        if ((int)g + q >= 0 && (int)g + q < (int)wv) v = src[q];
+#pragma unroll
+        for (int e = 0; e < V; ++e) w[(q + Q) * V + e] = v[e];
+    }
+    vec o;
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+        real acc = c[0] * w[Q * V + e];
+#pragma unroll
+        for (int d = 1; d <= NB; ++d) acc = fma(c[d], w[Q * V + e - d] + w[Q * V + e + d], acc);
+        o[e] = acc;
+    }
+    reinterpret_cast<gptr<vec>>(to_global(out))[i] = o;
+}
+
 // ---------------------------------------------------------------- launchers
 
 // Depth (16-deep blocks) up to which the matrix rows stay in registers, and the
@@ -846,11 +899,30 @@ hipError_t launch_zconv(int nh, void* data, long pitch, int n, long nlines, cons
     return hipErrorInvalidValue;
 }
 
+template <typename real>
+hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int nb, const void* table, hipStream_t s) {
+    const int v = 16 / (int)sizeof(real);
+    if (nlines <= 0 || pitch <= 0 || pitch % v || nlines * pitch / v >= (1l << 32)) return hipErrorInvalidValue;
+    const unsigned wv = (unsigned)(pitch / v), total = (unsigned)(nlines * pitch / v);
+    const dim3 grid((total + 255) / 256), block(256);
+    switch (nb) {
+#define X(N_)                                                                                                 \
+    case N_:                                                                                                  \
+        hipLaunchKernelGGL((zband_kernel<real, N_>), grid, block, 0, s, (const real*)in, (real*)out, wv, total, \
+                           (const real*)table);                                                               \
+        return hipGetLastError();
+        X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+#undef X
+    }
+    return hipErrorInvalidValue;
+}
+
 #define PIPE_INST(real)                                                                                        \
     template hipError_t launch_sine<real>(const SineAxis&, bool, const void*, void*, int, int, long, long, long, \
                                           long, long, bool, hipStream_t, const GroupArgs*, int);          \
     template hipError_t launch_zconv<real>(int, void*, long, int, long, const void*, const TwiddleBank&,         \
-                                           hipStream_t, const GroupArgs*, int);
+                                           hipStream_t, const GroupArgs*, int);                                \
+    template hipError_t launch_zband<real>(const void*, void*, long, long, int, const void*, hipStream_t);
 #if PIPE_TU_FP32
 PIPE_INST(float)
 #endif

@@ -236,6 +236,15 @@ hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStrea
 hipError_t launch_modal_factors(double* out, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz, int nh,
                                 double a, double b, double hz, int igf, double scale, long line0, long nlines,
                                 hipStream_t st);
+// The factors themselves at r < rz, rz values per mode line, in plan precision.
+hipError_t launch_modal_band(void* out, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz,
+                             double a, double b, double hz, int igf, double scale, hipStream_t st);
+// out_k = sum over |d| <= nb of table[line][|d|] in_{k+d} on nlines lines of nz
+// values, pitch apart (a multiple of a 16-byte vector; values beyond nz are zero in
+// the input and unspecified in the output); in != out, nb <= kModalBandMax.
+constexpr int kModalBandMax = 16;
+template <typename real>
+hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int nb, const void* table, hipStream_t s);
 // Pair table rows from the packed spectra of those sequences (nlines x nh complex).
 hipError_t launch_modal_table(const void* spec, void* table, int real_bytes, int nh, long nlines, hipStream_t st);
 

@@ -90,6 +90,28 @@ def test_mode_counts_match_the_padded_transform(torch_cuda, modes, kind, prec):
             assert torch_cuda.equal(s, t)
 
 
+# direct sums (N <= 16), cut z convolutions beyond, the whole sum; one plane, rows of
+# less than a vector and not a whole number of vectors
+@pytest.mark.parametrize("nb", [0, 1, 2, 3, 4, 5, 8, 13, 16, 17, 40])
+@pytest.mark.parametrize("shape", [(18, 7, 22), (5, 33, 37), (4, 3, 1), (3, 2, 3), (35, 6, 64)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_banded_sums_match_eq18_oracle(torch_cuda, nb, shape, prec):
+    from oracle import fourterm
+    from paper_1111_4971_amd import pipe
+    log("sine modes banded %s %s N=%d" % (prec, shape, nb))
+    rho = _rho(shape)
+    for wall, modes in (((False, False), None), ((True, False), (4, 6))):
+        plan, g = _plan(shape, prec, wall, modes, band=nb)
+        assert plan.band == min(nb, shape[2] - 1) and plan.info.lz == 0
+        got = gpu_solve(plan, rho)
+        ref = fourterm.solve(oracle_input(rho, prec), *g, band=plan.band)
+        assert rel_l2(got, ref) <= TOL[prec] and rel_max(got, ref) <= TOL[prec]
+    hx, hy, hz, a, b, mx, my, kind = g
+    padded = pipe.GreenPlan(*shape, hx, hy, hz, a, b, kind=kind, precision=prec, mx=mx, my=my, band=nb,
+                            L=(plan.info.lx, plan.info.ly))
+    assert torch_cuda.equal(plan.spectra(), padded.spectra())
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_route_follows_the_geometry(torch_cuda, prec):
     """Off the lattice (spacing, offset) or with lengths of its own a mesh keeps the
@@ -100,9 +122,9 @@ def test_route_follows_the_geometry(torch_cuda, prec):
     for plan, modal in ((mk(hx, hy), True), (mk(np.nextafter(hx, 0), hy), True), (mk(hx * (1 - 1e-12), hy), False),
                         (mk(hx, 0.9 * hy), False), (mk(A / 11, B / 9), True), (mk(A / 13, hy), False),
                         (mk(A / 24, hy, offset=(A / 24, 0.0)), False), (mk(hx, hy, L=(0, 0, 24)), False),
-                        (mk(hx, hy, band=2), None)):
-        if modal is not None:
-            assert (plan.info.xtile == 0) == modal, (plan.info.hx, plan.info.hy)
+                        (mk(hx, hy, band=0), True), (mk(hx, 0.9 * hy, band=0), False),
+                        (mk(hx, hy, band=0, L=(24, 0)), False), (mk(hx, hy, band=0, keep_green=True), False)):
+        assert (plan.info.xtile == 0) == modal, (plan.info.hx, plan.info.hy)
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
