@@ -5,8 +5,8 @@ Workload: 128 x 128 x 512 mesh (padded 256 x 256 x 1024) in a 1 x 1 pipe,
 z-integrated Green function (IGF), 256 x 256 modes, charge = three seeded
 Gaussian sub-bunches sampled with 2^28 macroparticles and deposited by
 cloud-in-cell.  One step = one full solve (all five kernels: on this mesh,
-which fills the pipe's lattice, x and y sine transforms, z convolution, and the
-sine transforms back) of that charge, input already resident in HBM.  The Green spectra are built once
+which fills the pipe's lattice, x and y sine transforms, the z sum of every mode,
+and the sine transforms back) of that charge, input already resident in HBM.  The Green spectra are built once
 per plan before timing (the paper computes them once and reuses them).
 
 Prints ONE JSON line on stdout; progress goes to stderr.
@@ -28,8 +28,8 @@ HBM_PEAK_GBS = 8000.0
 PASS_NAMES = ["z_forward", "y_forward", "x_product", "y_inverse", "z_inverse"]
 KERNEL_NAMES = ["z_r2c_kernel", "strided_kernel<fwd>", "xprod_kernel", "strided_kernel<inv>", "z_c2r_kernel"]
 # the five kernels of a plan that solves in the sine modes of the cross-section
-SINE_PASS_NAMES = ["x_sines", "y_sines", "z_convolution", "y_sines_back", "x_sines_back"]
-SINE_KERNEL_NAMES = ["sine_kernel<fwd>", "sine_kernel<fwd>", "zconv_kernel", "sine_kernel<inv>", "sine_kernel<inv>"]
+SINE_PASS_NAMES = ["x_sines", "y_sines", "z_sum", "y_sines_back", "x_sines_back"]
+SINE_KERNEL_NAMES = ["sine_kernel<fwd>", "sine_kernel<fwd>", "zexp_kernel", "sine_kernel<inv>", "sine_kernel<inv>"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_three_bunch_cic.json")
 KERNEL_SOURCES = ["paper_1111_4971_amd/csrc/modal.hip", "paper_1111_4971_amd/csrc/passes.hip", "paper_1111_4971_amd/csrc/xprod.hip",
                   "paper_1111_4971_amd/csrc/pass_common.h", "paper_1111_4971_amd/csrc/fft_engine.h"]

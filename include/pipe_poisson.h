@@ -87,8 +87,8 @@ typedef struct pipe_plan_info {
     size_t spectra_bytes;    /* device bytes held by the plan's Green spectra               */
     double model_bytes;      /* algorithmic HBM bytes of one solve (all passes)             */
     double pass_bytes[5];    /* the same per pass: z-forward, y-forward, x+product,         */
-                             /* y-inverse, z-inverse; in the sine modes x, y sines, z       */
-                             /* convolution, y, x sines back                                */
+                             /* y-inverse, z-inverse; in the sine modes x, y sines, z sum,  */
+                             /* y, x sines back                                             */
     double build_ms;         /* wall time of the plan build (Green evaluation + spectra)    */
     double tune_ms;          /* PIPE_AUTOTUNE: the chosen lengths' measured ms per solve  */
                              /* (0 = taken from the cache; -1 = not tuned)                */

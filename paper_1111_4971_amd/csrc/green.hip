@@ -351,6 +351,51 @@ __global__ void modal_band_kernel(T* out, ModalGeometry q, int rz, long nlines) 
     if (i < nlines * rz) out[i] = (T)modal_factor(q, i / rz, (int)(i % rz));
 }
 
+// e^{-x} as hi + lo: the double nearest it, corrected by comparing its 2^s-th power
+// (in double-double) with e^{-2^s x}, whose argument is exact and whose own rounding
+// then counts 2^-s times.
+__device__ __forceinline__ void exp_hi_lo(double x, double* hi, double* lo) {
+    const double r = exp(-x);
+    double h = r, l = 0.0, y = x;
+    int s = 0;
+    for (; s < 9 && 2.0 * y <= 16.0; ++s, y *= 2.0) {
+        const double p = h * h, e = fma(h, h, -p) + 2.0 * h * l;
+        h = p + e;
+        l = (p - h) + e;
+    }
+    const double t = exp(-y);
+    *hi = r;
+    *lo = s == 0 ? 0.0 : r * ldexp(((t - h) - l) / h, -s);
+}
+
+// Rows of the z recursion (modal.hip): thread (line, exponential); exponential e
+// folds alias e % nex in x and e / nex in y (mode m' or 2N - m').
+template <typename T>
+__global__ void modal_exp_kernel(T* out, ModalGeometry q, int nex, int ney, int values, long nlines) {
+    const int ne = nex * ney;
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= nlines * ne) return;
+    const int e = (int)(i % ne);
+    const long line = i / ne;
+    T* row = out + line * (1 + ne * kZexpEntries);
+    T* o = row + 1 + e * kZexpEntries;
+    const int m1 = stored_mode((int)(line / q.nmy), (q.nmx + 1) / 2), n1 = stored_mode((int)(line % q.nmy), (q.nmy + 1) / 2);
+    const int m = e % nex ? 2 * (q.nax + 1) - m1 : m1, n = e / nex ? 2 * (q.nay + 1) - n1 : n1;
+    double hi = 0.0, lo = 0.0, c = 0.0, x = 0.0;
+    if (m <= q.mx && n <= q.my) {
+        const double km = (double)m / q.a, kn = (double)n / q.b;
+        const double kap = M_PI * sqrt(km * km + kn * kn);
+        x = kap * q.hz;
+        exp_hi_lo(x, &hi, &lo);
+        c = q.scale / kap * (q.igf ? igf_g(x, 1) : hi);
+    }
+    o[0] = (T)hi;
+    o[1] = sizeof(T) == 8 ? (T)lo : (T)(hi - (double)(T)hi + lo);
+    o[2] = (T)c;
+    for (int s = 0; s < 6; ++s) o[3 + s] = c == 0.0 ? (T)0 : (T)exp(-x * (double)(values << s));
+    if (e == 0) row[0] = (T)modal_factor(q, line, 0);
+}
+
 // Packed spectra of real even sequences (imaginary parts are rounding) -> pairs
 // ((t_k + t_{nh-k})/2, (t_k - t_{nh-k})/2) / (2 nh), k <= nh/2.
 template <typename T2, typename T>
@@ -463,6 +508,18 @@ hipError_t launch_modal_band(void* out, int real_bytes, const SineAxis& ax, cons
         hipLaunchKernelGGL(modal_band_kernel<double>, dim3(nb), dim3(256), 0, st, (double*)out, q, rz, nlines);
     else
         hipLaunchKernelGGL(modal_band_kernel<float>, dim3(nb), dim3(256), 0, st, (float*)out, q, rz, nlines);
+    return hipGetLastError();
+}
+
+hipError_t launch_modal_exp(void* table, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int nex,
+                            int ney, int values, double a, double b, double hz, int igf, double scale, hipStream_t st) {
+    const ModalGeometry q{ax.na, ax.nm, ay.na, ay.nm, mx, my, igf, a, b, hz, scale};
+    const long nlines = (long)ax.nm * ay.nm;
+    const unsigned nb = blocks_for(nlines * nex * ney, 256);
+    if (real_bytes == 8)
+        hipLaunchKernelGGL(modal_exp_kernel<double>, dim3(nb), dim3(256), 0, st, (double*)table, q, nex, ney, values, nlines);
+    else
+        hipLaunchKernelGGL(modal_exp_kernel<float>, dim3(nb), dim3(256), 0, st, (float*)table, q, nex, ney, values, nlines);
     return hipGetLastError();
 }
 

@@ -8,15 +8,16 @@
 // sign, so they fold onto m' = 1 .. N - 1.  A solve is then
 //   M1 x sine transform  (nx, ny, nz)   -> (nmx, ny, nzp)      [sine]
 //   M2 y sine transform  (nmx, ny, nzp) -> (nmx, nmy, nzp)     [sine]
-//   M3 z convolution of every mode line with its folded z factor, in place
-//      (real lines zero-padded to lz, one real spectrum per line)   [zconv]
+//   M3 z sum of every mode line with its folded z factor, in place: a recursion
+//      while few modes fold onto a line [zexp], else a convolution (real lines
+//      zero-padded, one real spectrum per line) [zconv]; banded plans a filter [zband]
 //   M4 y sine transform back, M5 x sine transform back to (nx, ny, nz),
-// with nothing padded in x and y: 11 n values move instead of the 35 n of the
+// with nothing padded in x and y: 10 n values move instead of the 35 n of the
 // padded transform (n = nx ny nz, the spectra included).  nzp is nz rounded up
 // to a 16-byte vector.  Whole solves, padded transform -> sine modes: 128x128x512
-// FP32 235 -> 110 us, FP64 456 -> 177 us; 256x256x1024 FP32 1853 -> 877 us;
-// 64x64x256 FP64 74 -> 41 us; errors against 64 bits no larger (FP32 1.5e-7
-// against 2.4e-7, 1.7e-7 against 1.9e-7).
+// FP32 235 -> 103 us, FP64 456 -> 160 us; 256x256x1024 FP32 1853 -> 765 us;
+// 64x64x256 FP64 74 -> 39 us; errors against 64 bits no larger (FP32 1.4e-7
+// against 2.2e-7).
 #include <algorithm>
 
 #include "pass_common.h"
@@ -728,6 +729,106 @@ void zconv_kernel(real* data, long pitch, int n, long nlines, const cplx<real>* 
     }
 }
 
+// ---------------------------------------------------------------- z recursion
+//
+// The z factor of every mode is an exponential beyond the first plane, W(d) = C
+// r^{d-1} for d >= 1 with r = e^{-kappa hz} (Eq. 9 as it stands, Eq. 15 with its
+// constant factor), and a mode line folds at most 2 x 2 of them while no more than
+// 2N modes are kept per axis.  The z convolution is then
+//   out_k = W(0) x_k + sum_e C_e (F_k + G_k),
+//   F_{k+1} = r F_k + x_k,  G_{k-1} = r G_k + x_k:
+// no transform, no padding and no spectra to read (2 n values move instead of 3 n).
+// Lane t of the P lanes of a line holds values t V .. t V + V - 1: it runs the two
+// recursions over its own values, the lanes' results are combined by log2(P) shifts
+// with weights r^{V 2^s}, and it runs them again from what comes in.  r is applied as
+// an unevaluated sum hi + lo: a single rounding of r is raised to the distance it
+// carries (FP32 errors up to 4x the transform's at kappa hz = 0.05; with it at most
+// 0.94x over kappa hz = 1e-4 .. 2).
+//
+// Measured: 16384 lines of 512, four exponentials, FP32 20 us (the z convolution 27),
+// FP64 43 us (60); 65536 lines of 1024, one exponential, FP32 125 us (236; a copy of
+// the lines takes 110).  16 values a lane instead of 8 up to 512: 22 and 54 us.
+template <typename real> __device__ __forceinline__ real lane_shift(real x, int idx, bool in) {
+    const real v = from_lane(x, idx);
+    return in ? v : (real)0;
+}
+// WAVE: a line per wavefront (P = 64); its table row is then the same for every lane
+// and comes by scalar loads.
+template <typename real, int V, int NE, bool WAVE>
+__global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n, long nlines, const real* table, int logp,
+                                                   const GroupArgs* __restrict__ group) {
+    constexpr int VW = 16 / sizeof(real), NV = V / VW, TE = kZexpEntries;
+    using vec = vecv<real, VW>;
+    if (group) {
+        data = (real*)group[blockIdx.z].out;
+        table = (const real*)group[blockIdx.z].table;
+    }
+    if constexpr (WAVE) logp = 6;
+    const int P = 1 << logp, t = threadIdx.x & (P - 1), lane = threadIdx.x & 63;
+    const long line = (long)blockIdx.x * (256 >> logp) + (threadIdx.x >> logp);
+    const bool active = line < nlines;
+    const long at = WAVE ? __builtin_amdgcn_readfirstlane((int)(active ? line : 0)) : (active ? line : 0);
+    const gptr<real> row = to_global(data) + at * pitch + t * V;
+    real x[V], o[V];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        vec v{};
+        if (t * V + q * VW < n) v = reinterpret_cast<gptr<const vec>>(row)[q];   // rows are padded to whole vectors
+#pragma unroll
+        for (int e = 0; e < VW; ++e) x[q * VW + e] = t * V + q * VW + e < n ? v[e] : (real)0;
+    }
+    const gptr<const real> tl = to_global(table) + at * (1 + NE * TE);
+    const real c0 = tl[0];
+#pragma unroll
+    for (int j = 0; j < V; ++j) o[j] = c0 * x[j];
+    real rh[NE], rl[NE], f[NE], g[NE];
+    auto step = [&](int e, real y, real xv) { return fma(rh[e], y, fma(rl[e], y, xv)); };
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        rh[e] = tl[1 + e * TE];
+        rl[e] = tl[2 + e * TE];
+        real s = 0, b = 0;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            s = step(e, s, x[j]);
+            b = step(e, b, x[V - 1 - j]);
+        }
+        f[e] = lane_shift(s, (lane - 1) * 4, t >= 1);
+        g[e] = lane_shift(b, (lane + 1) * 4, t + 1 < P);
+    }
+#pragma unroll
+    for (int s = 0; s < 6; ++s) {
+        if (s >= logp) break;
+        const int d = 1 << s;
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const real w = tl[4 + e * TE + s];
+            f[e] = fma(w, lane_shift(f[e], (lane - d) * 4, t >= d), f[e]);
+            g[e] = fma(w, lane_shift(g[e], (lane + d) * 4, t + d < P), g[e]);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+        const real c = tl[3 + e * TE];
+        real y = f[e], z = g[e];
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            o[j] = fma(c, y, o[j]);
+            y = step(e, y, x[j]);
+            o[V - 1 - j] = fma(c, z, o[V - 1 - j]);
+            z = step(e, z, x[V - 1 - j]);
+        }
+    }
+    if (!active) return;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+        vec v;
+#pragma unroll
+        for (int e = 0; e < VW; ++e) v[e] = o[q * VW + e];
+        if (t * V + q * VW < n) reinterpret_cast<gptr<vec>>(row)[q] = v;
+    }
+}
+
 // ---------------------------------------------------------------- neighbouring planes
 //
 // The z sum of a banded plan (Eq. 18) on the mode lines: a symmetric filter of 2 NB
@@ -899,6 +1000,37 @@ hipError_t launch_zconv(int nh, void* data, long pitch, int n, long nlines, cons
     return hipErrorInvalidValue;
 }
 
+template <typename real, int V>
+static hipError_t launch_zexp_v(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
+                                const GroupArgs* group, int ngroup) {
+    int logp = 0;
+    while ((V << logp) < n) ++logp;
+    if (logp > 6) return hipErrorInvalidValue;
+    const long per = 256 >> logp;
+    const dim3 grid((unsigned)((nlines + per - 1) / per), 1, (unsigned)ngroup), block(256);
+    switch (ne) {
+#define X(N_)                                                                                              \
+    case N_:                                                                                               \
+        if (logp == 6)                                                                                     \
+            hipLaunchKernelGGL((zexp_kernel<real, V, N_, true>), grid, block, 0, s, (real*)data, pitch, n, nlines, \
+                               (const real*)table, logp, group);                                           \
+        else                                                                                               \
+            hipLaunchKernelGGL((zexp_kernel<real, V, N_, false>), grid, block, 0, s, (real*)data, pitch, n, nlines, \
+                               (const real*)table, logp, group);                                           \
+        return hipGetLastError();
+        X(1) X(2) X(4)
+#undef X
+    }
+    return hipErrorInvalidValue;
+}
+template <typename real>
+hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
+                       const GroupArgs* group, int ngroup) {
+    if (nlines <= 0 || n < 1 || n > 1024 || pitch < n || pitch % (16 / (int)sizeof(real))) return hipErrorInvalidValue;
+    return zexp_values(n) == 16 ? launch_zexp_v<real, 16>(data, pitch, n, nlines, ne, table, s, group, ngroup)
+                                : launch_zexp_v<real, 8>(data, pitch, n, nlines, ne, table, s, group, ngroup);
+}
+
 template <typename real>
 hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int nb, const void* table, hipStream_t s) {
     const int v = 16 / (int)sizeof(real);
@@ -922,6 +1054,8 @@ hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int 
                                           long, long, bool, hipStream_t, const GroupArgs*, int);          \
     template hipError_t launch_zconv<real>(int, void*, long, int, long, const void*, const TwiddleBank&,         \
                                            hipStream_t, const GroupArgs*, int);                                \
+    template hipError_t launch_zexp<real>(void*, long, int, long, int, const void*, hipStream_t,                \
+                                          const GroupArgs*, int);                                              \
     template hipError_t launch_zband<real>(const void*, void*, long, long, int, const void*, hipStream_t);
 #if PIPE_TU_FP32
 PIPE_INST(float)

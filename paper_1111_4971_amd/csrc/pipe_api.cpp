@@ -273,6 +273,7 @@ struct pipe_plan_s {
     // then the default ones, used for the reported sizes alone
     bool modal = false;
     SineAxis sx{}, sy{};
+    int nex = 0, ney = 0;    // z recursion: exponentials a mode line folds per axis (0: z convolution)
     int znh = 0;             // half length of the z convolution (zconv_length(nz))
     void* frag = nullptr;
     double band_speedup = 0;  // banded build: measured 3-D solve time / banded solve time
@@ -520,35 +521,34 @@ bool modal_mesh(pipe_plan_s* p) {
            lattice_axis(p->ny, p->hy, p->b, p->y0, p->my, &p->sy);
 }
 
-// Sine matrices and the z table of a sine-mode plan (p->sx, p->sy set): the pair
-// table of the z convolution, cut beyond p->band planes in a banded plan, or the
-// factors themselves where the band is short enough to be summed directly.
-pipe_status_t build_modal(pipe_plan_s* p, hipStream_t st, bool keep_green) {
-    const size_t fx = sine_frag_elems(p->sx.na, p->sx.nm), fy = sine_frag_elems(p->sy.na, p->sy.nm);
-    HIP_TRY(dev_alloc(&p->frag, (fx + fy) * p->rb), "allocation (sine matrices)");
-    p->sx.frag = p->frag;
-    p->sy.frag = (char*)p->frag + fx * p->rb;
-    HIP_TRY(launch_sine_frag((void*)p->sx.frag, p->rb, p->sx.na, p->sx.nm, st), "sine matrices");
-    HIP_TRY(launch_sine_frag((void*)p->sy.frag, p->rb, p->sy.na, p->sy.nm, st), "sine matrices");
-    const long lines = (long)p->sx.nm * p->sy.nm;
-    const int igf = (p->kind & 0x0f) == PIPE_GREEN_IGF_Z, planes = p->band >= 0 ? p->band + 1 : p->nz;
-    // 1/(2 pi a b) of Eq. 9, the 4 of the sine products, the cell volume
-    const double scale = 4.0 / (2.0 * M_PI * p->a * p->b) * p->hx * p->hy * p->hz;
-    if (modal_direct(p)) {
-        p->table_elems = (size_t)planes * lines;
-        p->nyq_elems = 0;
-        HIP_TRY(dev_alloc(&p->table, p->table_elems * p->rb), "allocation (Green spectra)");
-        HIP_TRY(launch_modal_band(p->table, p->rb, p->sx, p->sy, p->mx, p->my, planes, p->a, p->b, p->hz, igf, scale, st),
-                "mode factors");
-        HIP_TRY(hipStreamSynchronize(st), "plan build");
-        return PIPE_OK;
-    }
-    const int nh = p->znh = zconv_length(p->nz), np = nh / 2 + 1;
-    if (nh < 0) return fail(PIPE_ERR_UNSUPPORTED_SIZE, "no z transform for nz = %d", p->nz);
-    p->table_elems = 2 * (size_t)np * lines;
+// How a sine-mode plan (p->sx, p->sy, p->band set) takes the z sum, and the size of its
+// table: directly where the band is short, else by recursion where a line folds at
+// most two modes per axis (up to 2N modes kept, the default) and the sum is whole,
+// else by a z convolution.
+pipe_status_t choose_modal_z(pipe_plan_s* p) {
+    const size_t lines = (size_t)p->sx.nm * p->sy.nm;
+    const int Nx = p->sx.na + 1, Ny = p->sy.na + 1;
+    p->nex = p->ney = p->znh = 0;
     p->nyq_elems = 0;
-    HIP_TRY(dev_alloc(&p->table, p->table_elems * p->rb), "allocation (Green spectra)");
-    Scratch s;
+    if (modal_direct(p)) {
+        p->table_elems = (size_t)(p->band + 1) * lines;
+    } else if (p->band < 0 && p->mx <= 2 * Nx && p->my <= 2 * Ny) {
+        p->nex = p->mx > Nx ? 2 : 1;
+        p->ney = p->my > Ny ? 2 : 1;
+        p->table_elems = (1 + (size_t)p->nex * p->ney * kZexpEntries) * lines;
+    } else {
+        p->znh = zconv_length(p->nz);
+        if (p->znh < 0) return fail(PIPE_ERR_UNSUPPORTED_SIZE, "no z transform for nz = %d", p->nz);
+        p->table_elems = 2 * (size_t)(p->znh / 2 + 1) * lines;
+    }
+    return PIPE_OK;
+}
+
+// The pair table of the z convolution: the factors as even sequences (zero beyond
+// `planes`), transformed.
+pipe_status_t build_modal_spectra(pipe_plan_s* p, int planes, int igf, double scale, Scratch& s, hipStream_t st) {
+    const int nh = p->znh, np = nh / 2 + 1;
+    const long lines = (long)p->sx.nm * p->sy.nm;
     // sequences and their spectra (in place), at most 512 MB of lines at a time
     const long chunk = std::min(lines, std::max(1L, (512L << 20) / (16L * nh)));
     double* buf;
@@ -562,9 +562,38 @@ pipe_status_t build_modal(pipe_plan_s* p, hipStream_t st, bool keep_green) {
         HIP_TRY(launch_modal_table(buf, (char*)p->table + (size_t)l0 * np * 2 * p->rb, p->rb, nh, nl, st),
                 "spectra compression");
     }
+    return PIPE_OK;
+}
+
+// Sine matrices and the z table of a sine-mode plan (p->sx, p->sy set): the factors of
+// a direct sum, the rows of the recursion, or the pair table of the z convolution (cut
+// beyond p->band planes in a banded plan).
+pipe_status_t build_modal(pipe_plan_s* p, hipStream_t st, bool keep_green) {
+    const size_t fx = sine_frag_elems(p->sx.na, p->sx.nm), fy = sine_frag_elems(p->sy.na, p->sy.nm);
+    HIP_TRY(dev_alloc(&p->frag, (fx + fy) * p->rb), "allocation (sine matrices)");
+    p->sx.frag = p->frag;
+    p->sy.frag = (char*)p->frag + fx * p->rb;
+    HIP_TRY(launch_sine_frag((void*)p->sx.frag, p->rb, p->sx.na, p->sx.nm, st), "sine matrices");
+    HIP_TRY(launch_sine_frag((void*)p->sy.frag, p->rb, p->sy.na, p->sy.nm, st), "sine matrices");
+    const int igf = (p->kind & 0x0f) == PIPE_GREEN_IGF_Z, planes = p->band >= 0 ? p->band + 1 : p->nz;
+    // 1/(2 pi a b) of Eq. 9, the 4 of the sine products, the cell volume
+    const double scale = 4.0 / (2.0 * M_PI * p->a * p->b) * p->hx * p->hy * p->hz;
+    pipe_status_t rs = choose_modal_z(p);
+    if (rs != PIPE_OK) return rs;
+    HIP_TRY(dev_alloc(&p->table, p->table_elems * p->rb), "allocation (Green spectra)");
+    Scratch s;
+    if (modal_direct(p))
+        HIP_TRY(launch_modal_band(p->table, p->rb, p->sx, p->sy, p->mx, p->my, planes, p->a, p->b, p->hz, igf, scale, st),
+                "mode factors");
+    else if (p->nex)
+        HIP_TRY(launch_modal_exp(p->table, p->rb, p->sx, p->sy, p->mx, p->my, p->nex, p->ney, zexp_values(p->nz), p->a,
+                                 p->b, p->hz, igf, scale, st),
+                "mode factors");
+    else if ((rs = build_modal_spectra(p, planes, igf, scale, s, st)) != PIPE_OK)
+        return rs;
     if (keep_green) {
         double* rbar;
-        pipe_status_t rs = eval_green_table(p, st, s, &rbar);
+        rs = eval_green_table(p, st, s, &rbar);
         if (rs == PIPE_OK) rs = keep_green_table(p, rbar, st);
         if (rs != PIPE_OK) return rs;
     }
@@ -778,6 +807,8 @@ pipe_status_t run_modal_passes(pipe_plan_s* p, const void* rho, void* phi, void*
     if (modal_direct(p)) {      // never grouped: a banded batch member runs by itself
         HIP_TRY(launch_zband<real>(B2, B1 + m.b3_off, nzp, lines, p->band, p->table, st), "z sum");
         B2 = B1 + m.b3_off;
+    } else if (p->nex) {
+        HIP_TRY(launch_zexp<real>(B2, nzp, nz, lines, p->nex * p->ney, p->table, st, g(2), n), "z recursion");
     } else {
         HIP_TRY(launch_zconv<real>(p->znh, B2, nzp, nz, lines, p->table, p->ctx->tw, st, g(2), n), "z convolution");
     }
@@ -1501,10 +1532,10 @@ pipe_status_t time_full_for(const pipe_plan_s* b, hipStream_t st, double* ms_out
     if (modal_mesh(&q)) {
         // its matrices, and a table of zeros of the right size
         q.modal = true;
-        q.znh = zconv_length(q.nz);
+        if ((s = choose_modal_z(&q)) != PIPE_OK) return s;
         q.ws_bytes = plan_ws_bytes(&q);
         const size_t fx = sine_frag_elems(q.sx.na, q.sx.nm), fy = sine_frag_elems(q.sy.na, q.sy.nm);
-        const size_t tab = (size_t)q.sx.nm * q.sy.nm * (q.znh / 2 + 1) * 2 * q.rb;
+        const size_t tab = q.table_elems * q.rb;
         Scratch sc;
         HIP_TRY(sc.get(&q.frag, (fx + fy) * q.rb), "band timing allocation");
         HIP_TRY(sc.get(&q.table, tab), "band timing allocation");
@@ -1978,7 +2009,8 @@ pipe_status_t pipe_batch_create(const pipe_plan_t* plans, int count, pipe_batch_
                 r->apad == p->apad && r->zcap == p->zcap && r->xnt == p->xnt && r->a1pad == p->a1pad &&
                 r->modal == p->modal &&
                 (!p->modal || (r->sx.na == p->sx.na && r->sx.nm == p->sx.nm && r->sy.na == p->sy.na &&
-                               r->sy.nm == p->sy.nm)))   // the same sine matrices
+                               r->sy.nm == p->sy.nm &&    // the same sine matrices and z kernel
+                               r->nex == p->nex && r->ney == p->ney)))
                 g = (int)k;
         }
         if (g < 0) {

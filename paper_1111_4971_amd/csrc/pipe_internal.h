@@ -227,6 +227,17 @@ inline int zconv_length(int n) {
 template <typename real>
 hipError_t launch_zconv(int nh, void* data, long pitch, int n, long nlines, const void* table, const TwiddleBank& tw,
                         hipStream_t s, const GroupArgs* group = nullptr, int ngroup = 1);
+// The same by recursion for lines of ne (1, 2 or 4) exponentials (n <= 1024): table
+// rows of 1 + ne kZexpEntries values, W(0) and per exponential r hi, r lo, C, r^{V
+// 2^s} for s < 6, V = zexp_values(n) the values of a lane.
+constexpr int kZexpEntries = 9;
+inline int zexp_values(int n) { return n > 512 ? 16 : 8; }
+template <typename real>
+hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
+                       const GroupArgs* group = nullptr, int ngroup = 1);
+// Table rows of launch_zexp; nex, ney (1 or 2): modes folded per axis.
+hipError_t launch_modal_exp(void* table, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int nex,
+                            int ney, int values, double a, double b, double hz, int igf, double scale, hipStream_t st);
 // Sine matrices of one axis into frag (green.hip).
 hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStream_t st);
 // Folded z factors of mode lines [line0, line0 + nlines) (line = x mode * nmy + y

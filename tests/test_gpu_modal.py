@@ -70,6 +70,26 @@ def test_every_z_length_matches_eq10_oracle(torch_cuda, nz, prec):
     assert rel_l2(got, ref) <= TOL[prec] and rel_max(got, ref) <= TOL[prec], rel_l2(got, ref)
 
 
+# the z recursion where e^{-kappa hz} is next to 1 over the whole mesh, ordinary, and
+# underflows; modes that fold onto one, two and four exponentials and beyond (transform)
+@pytest.mark.parametrize("hz", [1e-6, 1e-3, 0.02, 1.0, 30.0, 400.0])
+@pytest.mark.parametrize("modes", [(9, 9), (9, 30), (30, 9), (20, 18), (45, 18)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_plane_spacings_match_eq10_oracle(torch_cuda, hz, modes, prec):
+    from oracle import fourterm
+    from paper_1111_4971_amd import pipe
+    for kind in (0, 1):
+        shape = (10, 9, 130)
+        log("sine modes %s hz=%g modes=%s kind=%d" % (prec, hz, modes, kind))
+        g = (A / 11, B / 10, hz, A, B) + modes
+        plan = pipe.GreenPlan(*shape, *g[:5], kind=kind, precision=prec, mx=modes[0], my=modes[1])
+        rho = np.abs(_rho(shape))
+        got = gpu_solve(plan, rho)
+        ref = fourterm.solve(oracle_input(rho, prec), *g, kind)
+        assert rel_l2(got, ref) <= TOL[prec] and rel_max(got, ref) <= TOL[prec], rel_l2(got, ref)
+        assert rel_l2(got, ref) <= (1e-14 if prec == "fp64" else 1e-6), rel_l2(got, ref)
+
+
 # few modes (rectangular transforms), modes that fold once and several times
 @pytest.mark.parametrize("modes", [(1, 1), (3, 40), (20, 20), (39, 30), (40, 31), (200, 155)])
 @pytest.mark.parametrize("kind", [0, 1])
