@@ -369,7 +369,7 @@ __device__ __forceinline__ void exp_hi_lo(double x, double* hi, double* lo) {
 }
 
 // Rows of the z recursion (modal.hip): thread (line, exponential); exponential e
-// folds alias e % nex in x and e / nex in y (mode m' or 2N - m').
+// folds alias e % nex in x and e / nex in y (modes m', 2N - m', 2N + m', 4N - m').
 template <typename T>
 __global__ void modal_exp_kernel(T* out, ModalGeometry q, int nex, int ney, int values, long nlines) {
     const int ne = nex * ney;
@@ -380,7 +380,8 @@ __global__ void modal_exp_kernel(T* out, ModalGeometry q, int nex, int ney, int 
     T* row = out + line * (1 + ne * kZexpEntries);
     T* o = row + 1 + e * kZexpEntries;
     const int m1 = stored_mode((int)(line / q.nmy), (q.nmx + 1) / 2), n1 = stored_mode((int)(line % q.nmy), (q.nmy + 1) / 2);
-    const int m = e % nex ? 2 * (q.nax + 1) - m1 : m1, n = e / nex ? 2 * (q.nay + 1) - n1 : n1;
+    auto alias = [](int i, int m, int N) { return i % 2 ? (i + 1) * N - m : i * N + m; };
+    const int m = alias(e % nex, m1, q.nax + 1), n = alias(e / nex, n1, q.nay + 1);
     double hi = 0.0, lo = 0.0, c = 0.0, x = 0.0;
     if (m <= q.mx && n <= q.my) {
         const double km = (double)m / q.a, kn = (double)n / q.b;

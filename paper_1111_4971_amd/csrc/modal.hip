@@ -752,12 +752,76 @@ template <typename real> __device__ __forceinline__ real lane_shift(real x, int 
     const real v = from_lane(x, idx);
     return in ? v : (real)0;
 }
+// The recursion sum of one line from a lane's values x; tl: the line's table row with
+// ng groups of NE exponentials; t: lane of the line, lane: of the wave.
+template <typename real, int V, int NE, typename Row>
+__device__ __forceinline__ void zexp_line(const real* x, real* o, Row tl, int ng, int logp, int t, int lane) {
+    constexpr int TE = kZexpEntries;
+    const int P = 1 << logp;
+    const real c0 = tl[0];
+#pragma unroll
+    for (int j = 0; j < V; ++j) o[j] = c0 * x[j];
+    for (int q = 0; q < ng; ++q) {
+        const Row te = tl + 1 + q * NE * TE;
+        real rh[NE], rl[NE], f[NE], g[NE];
+        auto step = [&](int e, real y, real xv) { return fma(rh[e], y, fma(rl[e], y, xv)); };
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            rh[e] = te[e * TE];
+            rl[e] = te[1 + e * TE];
+            real s = 0, b = 0;
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                s = step(e, s, x[j]);
+                b = step(e, b, x[V - 1 - j]);
+            }
+            f[e] = lane_shift(s, (lane - 1) * 4, t >= 1);
+            g[e] = lane_shift(b, (lane + 1) * 4, t + 1 < P);
+        }
+#pragma unroll
+        for (int s = 0; s < 6; ++s) {
+            if (s >= logp) break;
+            const int d = 1 << s;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const real w = te[3 + e * TE + s];
+                f[e] = fma(w, lane_shift(f[e], (lane - d) * 4, t >= d), f[e]);
+                g[e] = fma(w, lane_shift(g[e], (lane + d) * 4, t + d < P), g[e]);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const real c = te[2 + e * TE];
+            real y = f[e], z = g[e];
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                o[j] = fma(c, y, o[j]);
+                y = step(e, y, x[j]);
+                o[V - 1 - j] = fma(c, z, o[V - 1 - j]);
+                z = step(e, z, x[V - 1 - j]);
+            }
+        }
+    }
+}
+// A lane's V values of a row of n (rows hold whole 16-byte vectors), zero beyond, and back.
+template <typename real, int V, typename P> __device__ __forceinline__ void zexp_load(real* x, P row, int k0, int n) {
+    constexpr int VW = 16 / sizeof(real);
+    using vec = vecv<real, VW>;
+#pragma unroll
+    for (int q = 0; q < V / VW; ++q) {
+        vec v{};
+        if (k0 + q * VW < n) v = *reinterpret_cast<gptr<const vec>>(row + k0 + q * VW);
+#pragma unroll
+        for (int e = 0; e < VW; ++e) x[q * VW + e] = k0 + q * VW + e < n ? v[e] : (real)0;
+    }
+}
+
 // WAVE: a line per wavefront (P = 64); its table row is then the same for every lane
 // and comes by scalar loads.
 template <typename real, int V, int NE, bool WAVE>
 __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n, long nlines, const real* table, int logp,
                                                    const GroupArgs* __restrict__ group) {
-    constexpr int VW = 16 / sizeof(real), NV = V / VW, TE = kZexpEntries;
+    constexpr int VW = 16 / sizeof(real), NV = V / VW;
     using vec = vecv<real, VW>;
     if (group) {
         data = (real*)group[blockIdx.z].out;
@@ -768,64 +832,187 @@ __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n
     const long line = (long)blockIdx.x * (256 >> logp) + (threadIdx.x >> logp);
     const bool active = line < nlines;
     const long at = WAVE ? __builtin_amdgcn_readfirstlane((int)(active ? line : 0)) : (active ? line : 0);
-    const gptr<real> row = to_global(data) + at * pitch + t * V;
+    const gptr<real> row = to_global(data) + at * pitch;
     real x[V], o[V];
-#pragma unroll
-    for (int q = 0; q < NV; ++q) {
-        vec v{};
-        if (t * V + q * VW < n) v = reinterpret_cast<gptr<const vec>>(row)[q];   // rows are padded to whole vectors
-#pragma unroll
-        for (int e = 0; e < VW; ++e) x[q * VW + e] = t * V + q * VW + e < n ? v[e] : (real)0;
-    }
-    const gptr<const real> tl = to_global(table) + at * (1 + NE * TE);
-    const real c0 = tl[0];
-#pragma unroll
-    for (int j = 0; j < V; ++j) o[j] = c0 * x[j];
-    real rh[NE], rl[NE], f[NE], g[NE];
-    auto step = [&](int e, real y, real xv) { return fma(rh[e], y, fma(rl[e], y, xv)); };
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-        rh[e] = tl[1 + e * TE];
-        rl[e] = tl[2 + e * TE];
-        real s = 0, b = 0;
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            s = step(e, s, x[j]);
-            b = step(e, b, x[V - 1 - j]);
-        }
-        f[e] = lane_shift(s, (lane - 1) * 4, t >= 1);
-        g[e] = lane_shift(b, (lane + 1) * 4, t + 1 < P);
-    }
-#pragma unroll
-    for (int s = 0; s < 6; ++s) {
-        if (s >= logp) break;
-        const int d = 1 << s;
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const real w = tl[4 + e * TE + s];
-            f[e] = fma(w, lane_shift(f[e], (lane - d) * 4, t >= d), f[e]);
-            g[e] = fma(w, lane_shift(g[e], (lane + d) * 4, t + d < P), g[e]);
-        }
-    }
-#pragma unroll
-    for (int e = 0; e < NE; ++e) {
-        const real c = tl[3 + e * TE];
-        real y = f[e], z = g[e];
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            o[j] = fma(c, y, o[j]);
-            y = step(e, y, x[j]);
-            o[V - 1 - j] = fma(c, z, o[V - 1 - j]);
-            z = step(e, z, x[V - 1 - j]);
-        }
-    }
+    zexp_load<real, V>(x, row, t * V, n);
+    zexp_line<real, V, NE>(x, o, to_global(table) + at * (1 + NE * kZexpEntries), 1, logp, t, lane);
     if (!active) return;
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
         vec v;
 #pragma unroll
         for (int e = 0; e < VW; ++e) v[e] = o[q * VW + e];
-        if (t * V + q * VW < n) reinterpret_cast<gptr<vec>>(row)[q] = v;
+        if (t * V + q * VW < n) reinterpret_cast<gptr<vec>>(row + t * V)[q] = v;
+    }
+}
+
+// ---------------------------------------------------------------- y, z, y of a plane
+//
+constexpr int kPlaneJobs = 3;      // 160 KB hold 40 jobs of 4 KB
+// M2 to M4 for one x mode in one block, where the (ny, nz) plane fits LDS: the y
+// sines, the z recursion of its mode lines and the y sines back, with the plane read
+// and written once (6 n values less traffic) and three launches a solve instead of
+// five.  Bound by the serial work of one block per plane (one product, the recursion,
+// one product: 128x32 FP32 rows take 11 us against 18 for the three launches); with a
+// wave taking all rows of its columns, lines of 32 left three of four waves idle (40 us
+// a 128x128x32 solve, now 26).  A wave's job is 16 rows of both parities in 16 V columns; the forward
+// product is in place, so its sums (kPlaneJobs a wave at most) stay in registers until
+// all waves have read.  T: 16-row tiles of half the rows.
+template <typename real, int T, int NE>
+__global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArgs* __restrict__ group) {
+    constexpr int V = 8 / sizeof(real), KP = 16 * T;
+    using S = Sine<real, true, V, true>;
+    using M = typename S::M;
+    using vec = typename S::vec;
+    using veca = typename S::veca;
+    using acc_t = typename S::acc_t;
+    constexpr int VW = 16 / sizeof(real);
+    using wide = vecv<real, VW>;
+    real* data = (real*)a.data;
+    const real* table = (const real*)a.table;
+    if (group) {
+        data = (real*)group[blockIdx.z].out;
+        table = (const real*)group[blockIdx.z].table;
+    }
+    extern __shared__ __align__(16) unsigned char smem[];
+    real* lds = reinterpret_cast<real*>(smem);         // [parity][KP rows][pitch]
+    const gptr<real> plane = to_global(data) + (long)blockIdx.x * a.ny * a.nzp;
+    const int lane = threadIdx.x % 64, nw = blockDim.x / 64, pitch = a.pitch;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    // rows in, folded
+    const int wv = a.nzp / VW;
+#pragma unroll 2
+    for (int i = threadIdx.x; i < KP * wv; i += blockDim.x) {
+        const int r = i / wv, k = (i % wv) * VW;
+        wide x{}, y{};
+        if (r < a.h) x = *reinterpret_cast<gptr<const wide>>(plane + (long)r * a.nzp + k);
+        if (r < a.he) y = *reinterpret_cast<gptr<const wide>>(plane + (long)(a.na - 1 - r) * a.nzp + k);
+        *reinterpret_cast<wide*>(lds + r * pitch + k) = x + y;
+        *reinterpret_cast<wide*>(lds + (KP + r) * pitch + k) = r < a.he ? x - y : wide{};
+    }
+    __syncthreads();
+    const int groups = (a.nzp + 16 * V - 1) / (16 * V);
+    // a lane's column of group cg; past the last column another of the group
+    auto column = [&](int cg) {
+        const int own = (cg * 16 + (lane & 15)) * V;
+        return own < a.nzp ? own : cg * 16 * V;
+    };
+    // sum[parity] of row tile rt (of nrt) over kbn 16-deep blocks
+    auto product = [&](const void* frag_, int nrt, int kbn, int rt, int col, acc_t (&sum)[2][V]) {
+        const gptr<const veca> frag = reinterpret_cast<gptr<const veca>>(to_global((const real*)frag_)) + lane;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            veca af[T][S::NA];
+            __builtin_amdgcn_sched_barrier(0);       // no loads of the next parity before this
+#pragma unroll
+            for (int kb = 0; kb < T; ++kb)
+#pragma unroll
+                for (int q = 0; q < S::NA; ++q)
+                    if (kb < kbn) af[kb][q] = frag[(((p * nrt + rt) * kbn + kb) * S::NA + q) * 64];
+#pragma unroll
+            for (int c = 0; c < V; ++c) sum[p][c] = acc_t{};
+#pragma unroll
+            for (int kb = 0; kb < T; ++kb) {
+                if (kb >= kbn) break;
+                vec b[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    b[s] = *reinterpret_cast<const vec*>(lds + (p * KP + kb * 16 + 4 * s + (lane >> 4)) * pitch + col);
+#pragma unroll
+                for (int c = 0; c < V; ++c) {
+                    acc_t c0 = M::mac(af[kb][0][0], velem<real, V>(b[0], c), acc_t{});
+                    acc_t c1 = M::mac(af[kb][2 / S::VA][2 % S::VA], velem<real, V>(b[2], c), acc_t{});
+                    c0 = M::mac(af[kb][1 / S::VA][1 % S::VA], velem<real, V>(b[1], c), c0);
+                    c1 = M::mac(af[kb][3 / S::VA][3 % S::VA], velem<real, V>(b[3], c), c1);
+                    sum[p][c] += c0 + c1;
+                }
+            }
+        }
+    };
+    {
+        acc_t sum[kPlaneJobs][2][V];
+#pragma unroll
+        for (int j = 0; j < kPlaneJobs; ++j) {
+            const int job = wave + j * nw, cg = job % groups, rt = job / groups;
+            if (rt >= a.tm) break;
+            product(a.fwd, a.tm, T, rt, column(cg), sum[j]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPlaneJobs; ++j) {
+            const int job = wave + j * nw, cg = job % groups, rt = job / groups;
+            if (rt >= a.tm) break;
+            const int col = (cg * 16 + (lane & 15)) * V;
+            if (col < a.nzp)
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        vec v;
+#pragma unroll
+                        for (int c = 0; c < V; ++c) vset<real, V>(v, c, sum[j][p][c][r]);
+                        *reinterpret_cast<vec*>(lds + (p * KP + rt * 16 + M::row(lane, r)) * pitch + col) = v;
+                    }
+        }
+    }
+    __syncthreads();
+    {
+        constexpr int VZ = 8;
+        const int P = 1 << a.logp, t = lane & (P - 1), per = 64 >> a.logp;
+        for (int l0 = wave * per; l0 < a.no + a.ne; l0 += nw * per) {      // the wave's lanes stay together
+            const int l = l0 + (lane >> a.logp);
+            const bool active = l < a.no + a.ne;
+            const int at = active ? l : 0;
+            real* row = lds + (at < a.no ? at : KP + at - a.no) * pitch;
+            real x[VZ], o[VZ];
+#pragma unroll
+            for (int q = 0; q < VZ / VW; ++q) {
+                wide v{};
+                if (t * VZ + q * VW < a.nz) v = *reinterpret_cast<const wide*>(row + t * VZ + q * VW);
+#pragma unroll
+                for (int e = 0; e < VW; ++e) x[q * VW + e] = t * VZ + q * VW + e < a.nz ? v[e] : (real)0;
+            }
+            const gptr<const real> tl = to_global(table) +
+                                        ((long)blockIdx.x * (a.no + a.ne) + at) * (1 + a.ng * NE * kZexpEntries);
+            zexp_line<real, VZ, NE>(x, o, tl, a.ng, a.logp, t, lane);
+            if (active) {
+#pragma unroll
+                for (int q = 0; q < VZ / VW; ++q) {
+                    wide v;
+#pragma unroll
+                    for (int e = 0; e < VW; ++e) v[e] = o[q * VW + e];
+                    if (t * VZ + q * VW < a.nz) *reinterpret_cast<wide*>(row + t * VZ + q * VW) = v;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    for (int job = wave; job < groups * T; job += nw) {
+        const int cg = job % groups, rt = job / groups;
+        acc_t sum[2][V];
+        product(a.inv, T, a.tm, rt, column(cg), sum);
+        const int col = (cg * 16 + (lane & 15)) * V;
+        if (col >= a.nzp) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = rt * 16 + M::row(lane, r);
+            vec o, e;
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                vset<real, V>(o, c, sum[0][c][r]);
+                vset<real, V>(e, c, sum[1][c][r]);
+            }
+            auto put = [&](int row, const vec& v) {
+                *reinterpret_cast<gptr<vec>>(plane + (long)row * a.nzp + col) = v;
+            };
+            if (i < a.he) {
+                put(i, o + e);
+                put(a.na - 1 - i, o - e);
+            } else if (i < a.h) {
+                put(i, o);
+            }
+            if (i == 0 && a.na < a.ny) put(a.na, vec{});     // a node row on the wall
+        }
     }
 }
 
@@ -1031,6 +1218,59 @@ hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const
                                 : launch_zexp_v<real, 8>(data, pitch, n, nlines, ne, table, s, group, ngroup);
 }
 
+template <typename real, int T>
+static hipError_t launch_plane_t(const PlaneArgs& a, int ne, unsigned lds, int nplanes, hipStream_t s,
+                                 const GroupArgs* group, int ngroup) {
+    // a wave per job: at least four (row loads, z lines), at most sixteen
+    const int jobs = (a.nzp + 16 * 8 / (int)sizeof(real) - 1) / (16 * 8 / (int)sizeof(real)) * T;
+    if (jobs > 16 * kPlaneJobs) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nplanes, 1, (unsigned)ngroup), block(64 * (jobs < 4 ? 4 : jobs > 16 ? 16 : jobs));
+    switch (ne) {
+#define X(N_)                                                                                                \
+    case N_: {                                                                                               \
+        if (lds > 65536) {                                                                                   \
+            const hipError_t e = hipFuncSetAttribute((const void*)plane_kernel<real, T, N_>,                 \
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  \
+            if (e != hipSuccess) return e;                                                                   \
+        }                                                                                                    \
+        hipLaunchKernelGGL((plane_kernel<real, T, N_>), grid, block, lds, s, a, group);                      \
+        return hipGetLastError();                                                                            \
+    }
+        X(1) X(2) X(4)
+#undef X
+    }
+    return hipErrorInvalidValue;
+}
+template <typename real>
+hipError_t launch_plane(const SineAxis& ay, int nplanes, void* data, int nz, int nzp, int ne, const void* table,
+                        hipStream_t s, const GroupArgs* group, int ngroup) {
+    const size_t lds = plane_lds_bytes(ay, nz, (int)sizeof(real));
+    if (nplanes <= 0 || nz < 1 || nzp < nz || nzp % (16 / (int)sizeof(real)) || !lds || ne < 1) return hipErrorInvalidValue;
+    PlaneArgs a{};
+    a.data = data;
+    a.table = table;
+    a.fwd = ay.frag;
+    a.inv = (const char*)ay.frag + sine_frag_elems(ay.na, ay.nm, false) * sizeof(real);
+    a.ny = ay.n; a.na = ay.na;
+    a.h = (ay.na + 1) / 2; a.he = ay.na / 2;
+    a.no = (ay.nm + 1) / 2; a.ne = ay.nm / 2;
+    a.tm = (a.no + 15) / 16;
+    a.nz = nz; a.nzp = nzp;
+    const int T = (a.h + 15) / 16;
+    a.pitch = (int)(lds / (2 * 16 * T) / sizeof(real));
+    a.logp = 0;
+    while ((8 << a.logp) < nz) ++a.logp;
+    const int per = ne < 4 ? ne : 4;
+    a.ng = ne / per;
+    switch (T) {
+        case 1: return launch_plane_t<real, 1>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
+        case 2: return launch_plane_t<real, 2>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
+        case 3: return launch_plane_t<real, 3>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
+        case 4: return launch_plane_t<real, 4>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <typename real>
 hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int nb, const void* table, hipStream_t s) {
     const int v = 16 / (int)sizeof(real);
@@ -1056,6 +1296,8 @@ hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int 
                                            hipStream_t, const GroupArgs*, int);                                \
     template hipError_t launch_zexp<real>(void*, long, int, long, int, const void*, hipStream_t,                \
                                           const GroupArgs*, int);                                              \
+    template hipError_t launch_plane<real>(const SineAxis&, int, void*, int, int, int, const void*, hipStream_t, \
+                                           const GroupArgs*, int);                                             \
     template hipError_t launch_zband<real>(const void*, void*, long, long, int, const void*, hipStream_t);
 #if PIPE_TU_FP32
 PIPE_INST(float)

@@ -274,6 +274,7 @@ struct pipe_plan_s {
     bool modal = false;
     SineAxis sx{}, sy{};
     int nex = 0, ney = 0;    // z recursion: exponentials a mode line folds per axis (0: z convolution)
+    bool plane = false;      // y sines, z recursion and y sines back in one launch per x mode
     int znh = 0;             // half length of the z convolution (zconv_length(nz))
     void* frag = nullptr;
     double band_speedup = 0;  // banded build: measured 3-D solve time / banded solve time
@@ -339,6 +340,11 @@ void plan_pass_bytes(const pipe_plan_s* p, double out[5]) {
         // x sines, y sines, z convolution (lines in place + pair table), y sines, x sines
         const double b1 = (double)p->sx.nm * p->ny * p->nz * rb, b2 = (double)p->sx.nm * p->sy.nm * p->nz * rb;
         out[0] = out[4] = phys + b1;
+        if (p->plane) {
+            out[1] = 2.0 * b1 + (double)p->table_elems * rb;
+            out[2] = out[3] = 0.0;
+            return;
+        }
         out[1] = out[3] = b1 + b2;
         out[2] = 2.0 * b2 + (double)p->table_elems * rb;
         return;
@@ -521,6 +527,17 @@ bool modal_mesh(pipe_plan_s* p) {
            lattice_axis(p->ny, p->hy, p->b, p->y0, p->my, &p->sy);
 }
 
+// Whether the y sines, z recursion and y sines back run in one launch, a block per
+// plane: where two blocks fit a CU's LDS, so that few planes are not much serial work
+// each, or where there are enough planes for the card.  Solves in us, one launch
+// against three (sizes x, y, z): up to 64 KB FP64 32x32x32 17.9 / 23.3, FP32 96x96x128
+// 32.8 / 36.9; above, FP64 64x64x256 51.7 / 44.0, 128x64x192 56.9 / 52.5, 192x64x192
+// 69.6 / 76.0, 256x64x256 95 / 109, FP32 512x128x256 281 / 290.
+bool modal_plane(const pipe_plan_s* p) {
+    const size_t lds = plane_lds_bytes(p->sy, p->nz, p->rb);
+    return lds && (lds <= 64 * 1024 || p->sx.nm >= 160);
+}
+
 // How a sine-mode plan (p->sx, p->sy, p->band set) takes the z sum, and the size of its
 // table: directly where the band is short, else by recursion where a line folds at
 // most two modes per axis (up to 2N modes kept, the default) and the sum is whole,
@@ -529,13 +546,18 @@ pipe_status_t choose_modal_z(pipe_plan_s* p) {
     const size_t lines = (size_t)p->sx.nm * p->sy.nm;
     const int Nx = p->sx.na + 1, Ny = p->sy.na + 1;
     p->nex = p->ney = p->znh = 0;
+    p->plane = false;
     p->nyq_elems = 0;
+    // modes folded per axis (a power of two; 0: more than four)
+    auto folds = [](int m, int N) { return m <= N ? 1 : m <= 2 * N ? 2 : m <= 4 * N ? 4 : 0; };
+    const int nex = folds(p->mx, Nx), ney = folds(p->my, Ny);
     if (modal_direct(p)) {
         p->table_elems = (size_t)(p->band + 1) * lines;
-    } else if (p->band < 0 && p->mx <= 2 * Nx && p->my <= 2 * Ny) {
-        p->nex = p->mx > Nx ? 2 : 1;
-        p->ney = p->my > Ny ? 2 : 1;
-        p->table_elems = (1 + (size_t)p->nex * p->ney * kZexpEntries) * lines;
+    } else if (p->band < 0 && nex * ney > 0 && (nex * ney <= 4 || modal_plane(p))) {
+        p->nex = nex;
+        p->ney = ney;
+        p->plane = modal_plane(p);
+        p->table_elems = (1 + (size_t)nex * ney * kZexpEntries) * lines;
     } else {
         p->znh = zconv_length(p->nz);
         if (p->znh < 0) return fail(PIPE_ERR_UNSUPPORTED_SIZE, "no z transform for nz = %d", p->nz);
@@ -586,7 +608,8 @@ pipe_status_t build_modal(pipe_plan_s* p, hipStream_t st, bool keep_green) {
         HIP_TRY(launch_modal_band(p->table, p->rb, p->sx, p->sy, p->mx, p->my, planes, p->a, p->b, p->hz, igf, scale, st),
                 "mode factors");
     else if (p->nex)
-        HIP_TRY(launch_modal_exp(p->table, p->rb, p->sx, p->sy, p->mx, p->my, p->nex, p->ney, zexp_values(p->nz), p->a,
+        HIP_TRY(launch_modal_exp(p->table, p->rb, p->sx, p->sy, p->mx, p->my, p->nex, p->ney,
+                                 p->plane ? 8 : zexp_values(p->nz), p->a,
                                  p->b, p->hz, igf, scale, st),
                 "mode factors");
     else if ((rs = build_modal_spectra(p, planes, igf, scale, s, st)) != PIPE_OK)
@@ -800,6 +823,16 @@ pipe_status_t run_modal_passes(pipe_plan_s* p, const void* rho, void* phi, void*
     HIP_TRY(launch_sine<real>(p->sx, false, rho, B1, nz, nzp, nz, (long)ny * nz, nzp, m.p1, ny, vec_in, st, g(0), n),
             "x sine transform");
     if (ev) HIP_TRY(hipEventRecord(ev[1], st), "event");
+    if (p->plane) {
+        HIP_TRY(launch_plane<real>(p->sy, p->sx.nm, B1, nz, nzp, p->nex * p->ney, p->table, st, g(1), n),
+                "y sine transforms and z recursion");
+        if (ev)     // the two passes that this launch includes take no time of their own
+            for (int i = 2; i < 5; ++i) HIP_TRY(hipEventRecord(ev[i], st), "event");
+        HIP_TRY(launch_sine<real>(p->sx, true, B1, phi, nz, nzp, nzp, m.p1, nz, (long)ny * nz, ny, vec_out, st, g(4), n),
+                "x sine transform back");
+        if (ev) HIP_TRY(hipEventRecord(ev[5], st), "event");
+        return PIPE_OK;
+    }
     HIP_TRY(launch_sine<real>(p->sy, false, B1, B2, nz, nzp, m.p1, nzp, m.p2, nzp, p->sx.nm, true, st, g(1), n),
             "y sine transform");
     if (ev) HIP_TRY(hipEventRecord(ev[2], st), "event");
@@ -2115,6 +2148,7 @@ pipe_status_t pipe_batch_solve(pipe_batch_t b, const void* const* rho, void* con
                     char* B2 = A1 + modal_layout(p).b2_off;
                     a[0 * m + k] = {rho[i], A1, nullptr, nullptr, 0.0};
                     a[1 * m + k] = {A1, B2, nullptr, nullptr, 0.0};
+                    if (p->plane) a[1 * m + k] = {A1, A1, p->table, nullptr, 0.0};
                     a[2 * m + k] = {B2, B2, p->table, nullptr, 0.0};
                     a[3 * m + k] = {B2, A1, nullptr, nullptr, 0.0};
                     a[4 * m + k] = {A1, phi[i], nullptr, nullptr, 0.0};

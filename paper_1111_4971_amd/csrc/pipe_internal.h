@@ -235,9 +235,30 @@ inline int zexp_values(int n) { return n > 512 ? 16 : 8; }
 template <typename real>
 hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
                        const GroupArgs* group = nullptr, int ngroup = 1);
-// Table rows of launch_zexp; nex, ney (1 or 2): modes folded per axis.
+// Table rows of launch_zexp and launch_plane; nex, ney (1, 2 or 4): modes folded per axis.
 hipError_t launch_modal_exp(void* table, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int nex,
                             int ney, int values, double a, double b, double hz, int igf, double scale, hipStream_t st);
+// M2 to M4 in one launch for planes (ny, nzp) that fit LDS: nplanes planes in place,
+// ne (1, 2, 4, 8 or 16) exponentials a line with 8 values a lane.  group entries: out
+// = the planes, table.
+struct PlaneArgs {
+    void* data;
+    const void *table, *fwd, *inv;
+    int ny, na, h, he, no, ne, tm, nz, nzp, pitch, logp, ng;
+};
+// LDS bytes of a plane, 0 if it has more than 128 rows, lines of more than 512 values or
+// does not fit: rows an odd number of 128 bytes apart, so that the four rows of an
+// operand read fall on different banks.
+inline size_t plane_lds_bytes(const SineAxis& ay, int nz, int real_bytes) {
+    const int v = 16 / real_bytes, T = ((ay.na + 1) / 2 + 15) / 16;
+    size_t units = ((size_t)(nz + v - 1) / v * 16 + 127) / 128;
+    units += units % 2 == 0;
+    const size_t bytes = 2 * 16 * (size_t)T * units * 128;
+    return T <= 4 && nz <= 512 && bytes <= 160 * 1024 ? bytes : 0;
+}
+template <typename real>
+hipError_t launch_plane(const SineAxis& ay, int nplanes, void* data, int nz, int nzp, int ne, const void* table,
+                        hipStream_t s, const GroupArgs* group = nullptr, int ngroup = 1);
 // Sine matrices of one axis into frag (green.hip).
 hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStream_t st);
 // Folded z factors of mode lines [line0, line0 + nlines) (line = x mode * nmy + y

@@ -90,6 +90,26 @@ def test_plane_spacings_match_eq10_oracle(torch_cuda, hz, modes, prec):
         assert rel_l2(got, ref) <= (1e-14 if prec == "fp64" else 1e-6), rel_l2(got, ref)
 
 
+# the y sines, z recursion and y sines back in one launch and in three: both sides of
+# 64 KB of LDS at every number of row tiles (zmax: the longest FP32 lines within it),
+# one column, part of a column group; planes enough for the large ones; modes that fold
+# onto up to 16 exponentials
+@pytest.mark.parametrize("ny,zmax", [(15, 480), (32, 480), (33, 224), (64, 224), (65, 160), (96, 160), (97, 96), (128, 96)])
+@pytest.mark.parametrize("nx", [3, 161])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_planes_match_the_padded_transform(torch_cuda, ny, zmax, nx, prec):
+    zmax = zmax // 2 if prec == "fp64" else zmax
+    for nz, modes in ((1, None), (37, (2 * nx + 1, 4 * ny)), (zmax - 1, (4 * nx, 3 * ny)), (zmax, None), (zmax + 1, None)):
+        shape, wall = (nx, ny, nz), (nz % 2 == 0, nz % 2 == 1)
+        log("planes %s %s modes=%s" % (prec, shape, modes))
+        p, _ = _plan(shape, prec, wall, modes)
+        q, _ = _plan(shape, prec, wall, modes, padded=True)
+        rho = _rho(shape)
+        got, ref = gpu_solve(p, rho), gpu_solve(q, rho)
+        assert rel_l2(got, ref) <= 2 * TOL[prec] and rel_max(got, ref) <= 2 * TOL[prec], (shape, rel_l2(got, ref))
+        p.close(), q.close()
+
+
 # few modes (rectangular transforms), modes that fold once and several times
 @pytest.mark.parametrize("modes", [(1, 1), (3, 40), (20, 20), (39, 30), (40, 31), (200, 155)])
 @pytest.mark.parametrize("kind", [0, 1])
