@@ -346,9 +346,11 @@ __global__ void modal_factors_kernel(double* out, ModalGeometry q, int rz, int n
 
 // The factors at plane distances s < rz themselves, rz per line.
 template <typename T>
-__global__ void modal_band_kernel(T* out, ModalGeometry q, int rz, long nlines) {
+__global__ void modal_band_kernel(T* out, ModalGeometry q, int rz, int pitch, int lead, long nlines) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nlines * rz) out[i] = (T)modal_factor(q, i / rz, (int)(i % rz));
+    if (i >= nlines * pitch) return;
+    const int c = (int)(i % pitch), r = c ? c - lead : 0;
+    out[i] = r >= 0 && r < rz ? (T)modal_factor(q, i / pitch, r) : (T)0;
 }
 
 // e^{-x} as hi + lo: the double nearest it, corrected by comparing its 2^s-th power
@@ -371,8 +373,7 @@ __device__ __forceinline__ void exp_hi_lo(double x, double* hi, double* lo) {
 // Rows of the z recursion (modal.hip): thread (line, exponential); exponential e
 // folds alias e % nex in x and e / nex in y (modes m', 2N - m', 2N + m', 4N - m').
 template <typename T>
-__global__ void modal_exp_kernel(T* out, ModalGeometry q, int nex, int ney, int values, long nlines) {
-    const int ne = nex * ney;
+__global__ void modal_exp_kernel(T* out, ModalGeometry q, int nex, int ne, int values, long nlines) {
     const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nlines * ne) return;
     const int e = (int)(i % ne);
@@ -501,26 +502,27 @@ hipError_t launch_modal_factors(double* out, const SineAxis& ax, const SineAxis&
 }
 
 hipError_t launch_modal_band(void* out, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz,
-                             double a, double b, double hz, int igf, double scale, hipStream_t st) {
+                             double a, double b, double hz, int igf, double scale, int pitch, int lead,
+                             hipStream_t st) {
     const ModalGeometry q{ax.na, ax.nm, ay.na, ay.nm, mx, my, igf, a, b, hz, scale};
     const long nlines = (long)ax.nm * ay.nm;
-    const unsigned nb = blocks_for(nlines * rz, 256);
+    const unsigned nb = blocks_for(nlines * pitch, 256);
     if (real_bytes == 8)
-        hipLaunchKernelGGL(modal_band_kernel<double>, dim3(nb), dim3(256), 0, st, (double*)out, q, rz, nlines);
+        hipLaunchKernelGGL(modal_band_kernel<double>, dim3(nb), dim3(256), 0, st, (double*)out, q, rz, pitch, lead, nlines);
     else
-        hipLaunchKernelGGL(modal_band_kernel<float>, dim3(nb), dim3(256), 0, st, (float*)out, q, rz, nlines);
+        hipLaunchKernelGGL(modal_band_kernel<float>, dim3(nb), dim3(256), 0, st, (float*)out, q, rz, pitch, lead, nlines);
     return hipGetLastError();
 }
 
 hipError_t launch_modal_exp(void* table, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int nex,
-                            int ney, int values, double a, double b, double hz, int igf, double scale, hipStream_t st) {
+                            int ne, int values, double a, double b, double hz, int igf, double scale, hipStream_t st) {
     const ModalGeometry q{ax.na, ax.nm, ay.na, ay.nm, mx, my, igf, a, b, hz, scale};
     const long nlines = (long)ax.nm * ay.nm;
-    const unsigned nb = blocks_for(nlines * nex * ney, 256);
+    const unsigned nb = blocks_for(nlines * ne, 256);
     if (real_bytes == 8)
-        hipLaunchKernelGGL(modal_exp_kernel<double>, dim3(nb), dim3(256), 0, st, (double*)table, q, nex, ney, values, nlines);
+        hipLaunchKernelGGL(modal_exp_kernel<double>, dim3(nb), dim3(256), 0, st, (double*)table, q, nex, ne, values, nlines);
     else
-        hipLaunchKernelGGL(modal_exp_kernel<float>, dim3(nb), dim3(256), 0, st, (float*)table, q, nex, ney, values, nlines);
+        hipLaunchKernelGGL(modal_exp_kernel<float>, dim3(nb), dim3(256), 0, st, (float*)table, q, nex, ne, values, nlines);
     return hipGetLastError();
 }
 

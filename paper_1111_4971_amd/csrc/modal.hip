@@ -820,7 +820,7 @@ template <typename real, int V, typename P> __device__ __forceinline__ void zexp
 // and comes by scalar loads.
 template <typename real, int V, int NE, bool WAVE>
 __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n, long nlines, const real* table, int logp,
-                                                   const GroupArgs* __restrict__ group) {
+                                                   int ng, const GroupArgs* __restrict__ group) {
     constexpr int VW = 16 / sizeof(real), NV = V / VW;
     using vec = vecv<real, VW>;
     if (group) {
@@ -835,7 +835,7 @@ __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n
     const gptr<real> row = to_global(data) + at * pitch;
     real x[V], o[V];
     zexp_load<real, V>(x, row, t * V, n);
-    zexp_line<real, V, NE>(x, o, to_global(table) + at * (1 + NE * kZexpEntries), 1, logp, t, lane);
+    zexp_line<real, V, NE>(x, o, to_global(table) + at * (1 + ng * NE * kZexpEntries), ng, logp, t, lane);
     if (!active) return;
 #pragma unroll
     for (int q = 0; q < NV; ++q) {
@@ -846,21 +846,23 @@ __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n
     }
 }
 
-// ---------------------------------------------------------------- y, z, y of a plane
+// ---------------------------------------------------------------- sines, z, sines of a plane
 //
+// M2 to M4 in one block for one mode of the outer axis, where a plane (rows of the
+// other axis, nz) fits LDS: its sines, the z sum of its mode lines and its sines back,
+// with the plane read and written once (6 n values less traffic) and three launches a
+// solve instead of five.  Bound by the serial work of one block per plane (one product,
+// the z sum, one product: 128x32 FP32 rows take 11 us against 18 for three launches);
+// with a wave taking all rows of its columns, lines of 32 left three of four waves idle
+// (40 us a 128x128x32 solve, now 26).  A wave's job is 16 rows of both parities in 16 V
+// columns; the forward product is in place, so its sums (kPlaneJobs a wave at most)
+// stay in registers until all waves have read.  NE: exponentials of a recursion step,
+// 0: the z sum directly, by a window of 8 values a lane and 8 distances a step (thin
+// meshes fold many modes: 9x96x57 FP32 with 40 exponentials a line 47 us by recursion).
 constexpr int kPlaneJobs = 3;      // 160 KB hold 40 jobs of 4 KB
-// M2 to M4 for one x mode in one block, where the (ny, nz) plane fits LDS: the y
-// sines, the z recursion of its mode lines and the y sines back, with the plane read
-// and written once (6 n values less traffic) and three launches a solve instead of
-// five.  Bound by the serial work of one block per plane (one product, the recursion,
-// one product: 128x32 FP32 rows take 11 us against 18 for the three launches); with a
-// wave taking all rows of its columns, lines of 32 left three of four waves idle (40 us
-// a 128x128x32 solve, now 26).  A wave's job is 16 rows of both parities in 16 V columns; the forward
-// product is in place, so its sums (kPlaneJobs a wave at most) stay in registers until
-// all waves have read.  T: 16-row tiles of half the rows.
-template <typename real, int T, int NE>
+template <typename real, int NE>
 __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArgs* __restrict__ group) {
-    constexpr int V = 8 / sizeof(real), KP = 16 * T;
+    constexpr int V = 8 / sizeof(real), KC = 4;      // KC: 16-deep blocks of matrix rows in flight
     using S = Sine<real, true, V, true>;
     using M = typename S::M;
     using vec = typename S::vec;
@@ -868,64 +870,80 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
     using acc_t = typename S::acc_t;
     constexpr int VW = 16 / sizeof(real);
     using wide = vecv<real, VW>;
-    real* data = (real*)a.data;
+    const real* in = (const real*)a.in;
+    real* out = (real*)a.out;
     const real* table = (const real*)a.table;
     if (group) {
-        data = (real*)group[blockIdx.z].out;
+        in = out = (real*)group[blockIdx.z].out;
         table = (const real*)group[blockIdx.z].table;
     }
     extern __shared__ __align__(16) unsigned char smem[];
     real* lds = reinterpret_cast<real*>(smem);         // [parity][KP rows][pitch]
-    const gptr<real> plane = to_global(data) + (long)blockIdx.x * a.ny * a.nzp;
+    const int T = a.t, KP = 16 * T;
+    // this block's columns: wl from z0, of which w from hp are its own
+    const int z0 = (int)blockIdx.y * a.w - a.hp, wl = a.wl, klo = z0 < 0 ? -z0 : 0;
+    const int khi = min(wl, a.nz - z0), kend = min(a.hp + a.w, a.nzp - z0);
+    const gptr<const real> src = to_global(in) + blockIdx.x * a.ps + z0;
+    const gptr<real> dst = to_global(out) + blockIdx.x * a.ps + z0;
     const int lane = threadIdx.x % 64, nw = blockDim.x / 64, pitch = a.pitch;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
     // rows in, folded
-    const int wv = a.nzp / VW;
+    const int wv = wl / VW;
 #pragma unroll 2
     for (int i = threadIdx.x; i < KP * wv; i += blockDim.x) {
         const int r = i / wv, k = (i % wv) * VW;
         wide x{}, y{};
-        if (r < a.h) x = *reinterpret_cast<gptr<const wide>>(plane + (long)r * a.nzp + k);
-        if (r < a.he) y = *reinterpret_cast<gptr<const wide>>(plane + (long)(a.na - 1 - r) * a.nzp + k);
+        const bool in_line = k >= klo && z0 + k < a.nzp;
+        if (in_line && r < a.h) x = *reinterpret_cast<gptr<const wide>>(src + r * a.rs + k);
+        if (in_line && r < a.he) y = *reinterpret_cast<gptr<const wide>>(src + (a.na - 1 - r) * a.rs + k);
         *reinterpret_cast<wide*>(lds + r * pitch + k) = x + y;
         *reinterpret_cast<wide*>(lds + (KP + r) * pitch + k) = r < a.he ? x - y : wide{};
     }
     __syncthreads();
-    const int groups = (a.nzp + 16 * V - 1) / (16 * V);
-    // a lane's column of group cg; past the last column another of the group
-    auto column = [&](int cg) {
-        const int own = (cg * 16 + (lane & 15)) * V;
-        return own < a.nzp ? own : cg * 16 * V;
+    const int groups = (wl + 16 * V - 1) / (16 * V);
+    // a lane's column of group cg from k0 on; past the last column another of the group
+    auto column = [&](int k0, int cg) {
+        const int own = k0 + (cg * 16 + (lane & 15)) * V;
+        return own < wl ? own : k0 + cg * 16 * V;
     };
     // sum[parity] of row tile rt (of nrt) over kbn 16-deep blocks
     auto product = [&](const void* frag_, int nrt, int kbn, int rt, int col, acc_t (&sum)[2][V]) {
         const gptr<const veca> frag = reinterpret_cast<gptr<const veca>>(to_global((const real*)frag_)) + lane;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            veca af[T][S::NA];
-            __builtin_amdgcn_sched_barrier(0);       // no loads of the next parity before this
-#pragma unroll
-            for (int kb = 0; kb < T; ++kb)
-#pragma unroll
-                for (int q = 0; q < S::NA; ++q)
-                    if (kb < kbn) af[kb][q] = frag[(((p * nrt + rt) * kbn + kb) * S::NA + q) * 64];
 #pragma unroll
             for (int c = 0; c < V; ++c) sum[p][c] = acc_t{};
+#pragma unroll 1
+            for (int k0 = 0; k0 < kbn; k0 += KC) {
+                veca af[KC][S::NA];
+                acc_t part[V];
+                __builtin_amdgcn_sched_barrier(0);       // no loads of the next parity before this
 #pragma unroll
-            for (int kb = 0; kb < T; ++kb) {
-                if (kb >= kbn) break;
-                vec b[4];
+                for (int k = 0; k < KC; ++k)
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    b[s] = *reinterpret_cast<const vec*>(lds + (p * KP + kb * 16 + 4 * s + (lane >> 4)) * pitch + col);
+                    for (int q = 0; q < S::NA; ++q)
+                        if (k0 + k < kbn) af[k][q] = frag[(((p * nrt + rt) * kbn + k0 + k) * S::NA + q) * 64];
 #pragma unroll
-                for (int c = 0; c < V; ++c) {
-                    acc_t c0 = M::mac(af[kb][0][0], velem<real, V>(b[0], c), acc_t{});
-                    acc_t c1 = M::mac(af[kb][2 / S::VA][2 % S::VA], velem<real, V>(b[2], c), acc_t{});
-                    c0 = M::mac(af[kb][1 / S::VA][1 % S::VA], velem<real, V>(b[1], c), c0);
-                    c1 = M::mac(af[kb][3 / S::VA][3 % S::VA], velem<real, V>(b[3], c), c1);
-                    sum[p][c] += c0 + c1;
+                for (int c = 0; c < V; ++c) part[c] = acc_t{};
+#pragma unroll
+                for (int k = 0; k < KC; ++k) {
+                    if (k0 + k >= kbn) break;
+                    vec b[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s)
+                        b[s] = *reinterpret_cast<const vec*>(lds + (p * KP + (k0 + k) * 16 + 4 * s + (lane >> 4)) * pitch +
+                                                             col);
+#pragma unroll
+                    for (int c = 0; c < V; ++c) {
+                        acc_t c0 = M::mac(af[k][0][0], velem<real, V>(b[0], c), acc_t{});
+                        acc_t c1 = M::mac(af[k][2 / S::VA][2 % S::VA], velem<real, V>(b[2], c), acc_t{});
+                        c0 = M::mac(af[k][1 / S::VA][1 % S::VA], velem<real, V>(b[1], c), c0);
+                        c1 = M::mac(af[k][3 / S::VA][3 % S::VA], velem<real, V>(b[3], c), c1);
+                        part[c] += c0 + c1;
+                    }
                 }
+#pragma unroll
+                for (int c = 0; c < V; ++c) sum[p][c] += part[c];
             }
         }
     };
@@ -935,7 +953,7 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
         for (int j = 0; j < kPlaneJobs; ++j) {
             const int job = wave + j * nw, cg = job % groups, rt = job / groups;
             if (rt >= a.tm) break;
-            product(a.fwd, a.tm, T, rt, column(cg), sum[j]);
+            product(a.fwd, a.tm, T, rt, column(0, cg), sum[j]);
         }
         __syncthreads();
 #pragma unroll
@@ -943,7 +961,7 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
             const int job = wave + j * nw, cg = job % groups, rt = job / groups;
             if (rt >= a.tm) break;
             const int col = (cg * 16 + (lane & 15)) * V;
-            if (col < a.nzp)
+            if (col < wl)
 #pragma unroll
                 for (int p = 0; p < 2; ++p)
 #pragma unroll
@@ -958,41 +976,78 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
     __syncthreads();
     {
         constexpr int VZ = 8;
-        const int P = 1 << a.logp, t = lane & (P - 1), per = 64 >> a.logp;
-        for (int l0 = wave * per; l0 < a.no + a.ne; l0 += nw * per) {      // the wave's lanes stay together
+        const int P = 1 << a.logp, t = lane & (P - 1), per = 64 >> a.logp, lines = a.no + a.ne;
+        for (int l0 = wave * per; l0 < lines; l0 += nw * per) {      // the wave's lanes stay together
             const int l = l0 + (lane >> a.logp);
-            const bool active = l < a.no + a.ne;
-            const int at = active ? l : 0;
+            const bool active = l < lines;
+            const int at = active ? l : l0;
             real* row = lds + (at < a.no ? at : KP + at - a.no) * pitch;
+            auto get = [&](real* x, int k0) {      // 8 values from k0 (a multiple of 8), zero outside the line
+#pragma unroll
+                for (int q = 0; q < VZ / VW; ++q) {
+                    const int k = k0 + q * VW;
+                    wide v{};
+                    if (k >= klo && k < khi) v = *reinterpret_cast<const wide*>(row + k);
+#pragma unroll
+                    for (int e = 0; e < VW; ++e) x[q * VW + e] = k + e < khi ? v[e] : (real)0;
+                }
+            };
             real x[VZ], o[VZ];
+            get(x, t * VZ);
+            const gptr<const real> tl = to_global(table) + blockIdx.x * a.tp + at * a.tl;
+            if constexpr (NE > 0) {
+                zexp_line<real, VZ, NE>(x, o, tl, a.ng, a.logp, t, lane);
+            } else {
+                const real c0 = tl[0];
+                real lo[VZ], hi[VZ];
 #pragma unroll
-            for (int q = 0; q < VZ / VW; ++q) {
-                wide v{};
-                if (t * VZ + q * VW < a.nz) v = *reinterpret_cast<const wide*>(row + t * VZ + q * VW);
+                for (int i = 0; i < VZ; ++i) {
+                    o[i] = c0 * x[i];
+                    lo[i] = hi[i] = x[i];
+                }
+#pragma unroll(sizeof(real) == 4 ? 2 : 1)
+                for (int jb = 1; jb <= a.ng; ++jb) {
+                    real c[VZ], u[VZ], w[VZ];
 #pragma unroll
-                for (int e = 0; e < VW; ++e) x[q * VW + e] = t * VZ + q * VW + e < a.nz ? v[e] : (real)0;
+                    for (int q = 0; q < VZ / VW; ++q) {
+                        const wide v = reinterpret_cast<gptr<const wide>>(tl + jb * VZ)[q];
+#pragma unroll
+                        for (int e = 0; e < VW; ++e) c[q * VW + e] = v[e];
+                    }
+                    get(u, (t - jb) * VZ);
+                    get(w, (t + jb) * VZ);
+#pragma unroll
+                    for (int j = 1; j <= VZ; ++j)
+#pragma unroll
+                        for (int i = 0; i < VZ; ++i)
+                            o[i] = fma(c[j - 1], (i >= j ? lo[i - j] : u[VZ + i - j]) + (i + j < VZ ? hi[i + j] : w[i + j - VZ]),
+                                       o[i]);
+#pragma unroll
+                    for (int i = 0; i < VZ; ++i) {
+                        lo[i] = u[i];
+                        hi[i] = w[i];
+                    }
+                }
             }
-            const gptr<const real> tl = to_global(table) +
-                                        ((long)blockIdx.x * (a.no + a.ne) + at) * (1 + a.ng * NE * kZexpEntries);
-            zexp_line<real, VZ, NE>(x, o, tl, a.ng, a.logp, t, lane);
             if (active) {
 #pragma unroll
                 for (int q = 0; q < VZ / VW; ++q) {
                     wide v;
 #pragma unroll
                     for (int e = 0; e < VW; ++e) v[e] = o[q * VW + e];
-                    if (t * VZ + q * VW < a.nz) *reinterpret_cast<wide*>(row + t * VZ + q * VW) = v;
+                    if (t * VZ + q * VW < khi) *reinterpret_cast<wide*>(row + t * VZ + q * VW) = v;
                 }
             }
         }
     }
     __syncthreads();
-    for (int job = wave; job < groups * T; job += nw) {
-        const int cg = job % groups, rt = job / groups;
+    const int own = (a.w + 16 * V - 1) / (16 * V);
+    for (int job = wave; job < own * T; job += nw) {
+        const int cg = job % own, rt = job / own;
         acc_t sum[2][V];
-        product(a.inv, T, a.tm, rt, column(cg), sum);
-        const int col = (cg * 16 + (lane & 15)) * V;
-        if (col >= a.nzp) continue;
+        product(a.inv, T, a.tm, rt, column(a.hp, cg), sum);
+        const int col = a.hp + (cg * 16 + (lane & 15)) * V;
+        if (col >= kend) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = rt * 16 + M::row(lane, r);
@@ -1003,7 +1058,7 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
                 vset<real, V>(e, c, sum[1][c][r]);
             }
             auto put = [&](int row, const vec& v) {
-                *reinterpret_cast<gptr<vec>>(plane + (long)row * a.nzp + col) = v;
+                *reinterpret_cast<gptr<vec>>(dst + row * a.rs + col) = v;
             };
             if (i < a.he) {
                 put(i, o + e);
@@ -1011,7 +1066,7 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
             } else if (i < a.h) {
                 put(i, o);
             }
-            if (i == 0 && a.na < a.ny) put(a.na, vec{});     // a node row on the wall
+            if (i == 0 && a.na < a.n) put(a.na, vec{});      // a node row on the wall
         }
     }
 }
@@ -1195,15 +1250,16 @@ static hipError_t launch_zexp_v(void* data, long pitch, int n, long nlines, int 
     if (logp > 6) return hipErrorInvalidValue;
     const long per = 256 >> logp;
     const dim3 grid((unsigned)((nlines + per - 1) / per), 1, (unsigned)ngroup), block(256);
-    switch (ne) {
+    const int ng = ne > 4 ? ne / 4 : 1;
+    switch (ne > 4 ? 4 : ne) {
 #define X(N_)                                                                                              \
     case N_:                                                                                               \
         if (logp == 6)                                                                                     \
             hipLaunchKernelGGL((zexp_kernel<real, V, N_, true>), grid, block, 0, s, (real*)data, pitch, n, nlines, \
-                               (const real*)table, logp, group);                                           \
+                               (const real*)table, logp, ng, group);                                       \
         else                                                                                               \
             hipLaunchKernelGGL((zexp_kernel<real, V, N_, false>), grid, block, 0, s, (real*)data, pitch, n, nlines, \
-                               (const real*)table, logp, group);                                           \
+                               (const real*)table, logp, ng, group);                                       \
         return hipGetLastError();
         X(1) X(2) X(4)
 #undef X
@@ -1218,55 +1274,59 @@ hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const
                                 : launch_zexp_v<real, 8>(data, pitch, n, nlines, ne, table, s, group, ngroup);
 }
 
-template <typename real, int T>
-static hipError_t launch_plane_t(const PlaneArgs& a, int ne, unsigned lds, int nplanes, hipStream_t s,
-                                 const GroupArgs* group, int ngroup) {
+template <typename real>
+hipError_t launch_plane(const SineAxis& ax, const PlaneSplit& split, long rs, long ps, int nplanes, const void* in,
+                        void* out, int nz, int nzp, int ne, int nb, const void* table, long line_stride,
+                        long plane_stride, hipStream_t s, const GroupArgs* group, int ngroup) {
+    constexpr int VW = 16 / sizeof(real);
+    const bool whole = split.w >= nz;
+    const int wl = whole ? nzp : split.w + 2 * split.hp;
+    const size_t lds = plane_lds_bytes(ax, wl, (int)sizeof(real));
+    if (nplanes <= 0 || nz < 1 || nzp < nz || nzp % VW || !lds || ne < 0 || nb < 0) return hipErrorInvalidValue;
+    // a part of the lines: whole lane windows, and the neighbours' planes that its sums reach
+    if (!whole && (split.w < 8 || split.w % 8 || split.hp < 8 * nb || split.hp % 8 || ne || in == out || group))
+        return hipErrorInvalidValue;
+    PlaneArgs a{};
+    a.in = in;
+    a.out = out;
+    a.table = table;
+    a.fwd = ax.frag;
+    a.inv = (const char*)ax.frag + sine_frag_elems(ax.na, ax.nm, false) * sizeof(real);
+    a.rs = rs; a.ps = ps;
+    a.n = ax.n; a.na = ax.na;
+    a.h = (ax.na + 1) / 2; a.he = ax.na / 2;
+    a.no = (ax.nm + 1) / 2; a.ne = ax.nm / 2;
+    a.tm = (a.no + 15) / 16;
+    a.t = (a.h + 15) / 16;
+    a.nz = nz; a.nzp = nzp;
+    a.w = whole ? nzp : split.w;
+    a.hp = whole ? 0 : split.hp;
+    a.wl = wl;
+    a.pitch = (int)(lds / (2 * 16 * a.t) / sizeof(real));
+    a.logp = 0;
+    while ((8 << a.logp) < (whole ? nz : wl)) ++a.logp;
+    const int per = ne < 4 ? ne : 4;
+    a.ng = per ? ne / per : nb;
+    const long row = plane_table_row(ne, nb);
+    a.tl = line_stride * row;
+    a.tp = plane_stride * row;
     // a wave per job: at least four (row loads, z lines), at most sixteen
-    const int jobs = (a.nzp + 16 * 8 / (int)sizeof(real) - 1) / (16 * 8 / (int)sizeof(real)) * T;
+    const int jobs = (wl + 16 * 8 / (int)sizeof(real) - 1) / (16 * 8 / (int)sizeof(real)) * a.t;
     if (jobs > 16 * kPlaneJobs) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)nplanes, 1, (unsigned)ngroup), block(64 * (jobs < 4 ? 4 : jobs > 16 ? 16 : jobs));
-    switch (ne) {
+    const dim3 grid((unsigned)nplanes, (unsigned)((nz + a.w - 1) / a.w), (unsigned)ngroup), block(64 * (jobs < 4 ? 4 : jobs > 16 ? 16 : jobs));
+    switch (per) {
 #define X(N_)                                                                                                \
     case N_: {                                                                                               \
         if (lds > 65536) {                                                                                   \
-            const hipError_t e = hipFuncSetAttribute((const void*)plane_kernel<real, T, N_>,                 \
+            const hipError_t e = hipFuncSetAttribute((const void*)plane_kernel<real, N_>,                    \
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  \
             if (e != hipSuccess) return e;                                                                   \
         }                                                                                                    \
-        hipLaunchKernelGGL((plane_kernel<real, T, N_>), grid, block, lds, s, a, group);                      \
+        hipLaunchKernelGGL((plane_kernel<real, N_>), grid, block, lds, s, a, group);                         \
         return hipGetLastError();                                                                            \
     }
-        X(1) X(2) X(4)
+        X(0) X(1) X(2) X(4)
 #undef X
-    }
-    return hipErrorInvalidValue;
-}
-template <typename real>
-hipError_t launch_plane(const SineAxis& ay, int nplanes, void* data, int nz, int nzp, int ne, const void* table,
-                        hipStream_t s, const GroupArgs* group, int ngroup) {
-    const size_t lds = plane_lds_bytes(ay, nz, (int)sizeof(real));
-    if (nplanes <= 0 || nz < 1 || nzp < nz || nzp % (16 / (int)sizeof(real)) || !lds || ne < 1) return hipErrorInvalidValue;
-    PlaneArgs a{};
-    a.data = data;
-    a.table = table;
-    a.fwd = ay.frag;
-    a.inv = (const char*)ay.frag + sine_frag_elems(ay.na, ay.nm, false) * sizeof(real);
-    a.ny = ay.n; a.na = ay.na;
-    a.h = (ay.na + 1) / 2; a.he = ay.na / 2;
-    a.no = (ay.nm + 1) / 2; a.ne = ay.nm / 2;
-    a.tm = (a.no + 15) / 16;
-    a.nz = nz; a.nzp = nzp;
-    const int T = (a.h + 15) / 16;
-    a.pitch = (int)(lds / (2 * 16 * T) / sizeof(real));
-    a.logp = 0;
-    while ((8 << a.logp) < nz) ++a.logp;
-    const int per = ne < 4 ? ne : 4;
-    a.ng = ne / per;
-    switch (T) {
-        case 1: return launch_plane_t<real, 1>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
-        case 2: return launch_plane_t<real, 2>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
-        case 3: return launch_plane_t<real, 3>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
-        case 4: return launch_plane_t<real, 4>(a, per, (unsigned)lds, nplanes, s, group, ngroup);
     }
     return hipErrorInvalidValue;
 }
@@ -1296,8 +1356,8 @@ hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int 
                                            hipStream_t, const GroupArgs*, int);                                \
     template hipError_t launch_zexp<real>(void*, long, int, long, int, const void*, hipStream_t,                \
                                           const GroupArgs*, int);                                              \
-    template hipError_t launch_plane<real>(const SineAxis&, int, void*, int, int, int, const void*, hipStream_t, \
-                                           const GroupArgs*, int);                                             \
+    template hipError_t launch_plane<real>(const SineAxis&, const PlaneSplit&, long, long, int, const void*, void*, int, \
+                                           int, int, int, const void*, long, long, hipStream_t, const GroupArgs*, int); \
     template hipError_t launch_zband<real>(const void*, void*, long, long, int, const void*, hipStream_t);
 #if PIPE_TU_FP32
 PIPE_INST(float)

@@ -273,8 +273,10 @@ struct pipe_plan_s {
     // then the default ones, used for the reported sizes alone
     bool modal = false;
     SineAxis sx{}, sy{};
-    int nex = 0, ney = 0;    // z recursion: exponentials a mode line folds per axis (0: z convolution)
-    bool plane = false;      // y sines, z recursion and y sines back in one launch per x mode
+    int nexp = 0, nex = 0;   // z recursion: exponentials of a mode line, modes it folds in x (0: z convolution)
+    int plane = 0;           // sines, z sum, sines back of a plane in one launch: rows in y (1), x (2), not (0)
+    PlaneSplit split{};      // its parts of the lines
+    int zdir = 0;            // such a plane's direct z sum: 8 * zdir plane distances (nexp = 0)
     int znh = 0;             // half length of the z convolution (zconv_length(nz))
     void* frag = nullptr;
     double band_speedup = 0;  // banded build: measured 3-D solve time / banded solve time
@@ -341,7 +343,9 @@ void plan_pass_bytes(const pipe_plan_s* p, double out[5]) {
         const double b1 = (double)p->sx.nm * p->ny * p->nz * rb, b2 = (double)p->sx.nm * p->sy.nm * p->nz * rb;
         out[0] = out[4] = phys + b1;
         if (p->plane) {
-            out[1] = 2.0 * b1 + (double)p->table_elems * rb;
+            const double bp = p->plane == 1 ? b1 : (double)p->nx * p->sy.nm * p->nz * rb;
+            out[0] = out[4] = phys + bp;
+            out[1] = 2.0 * bp + (double)p->table_elems * rb;
             out[2] = out[3] = 0.0;
             return;
         }
@@ -527,37 +531,90 @@ bool modal_mesh(pipe_plan_s* p) {
            lattice_axis(p->ny, p->hy, p->b, p->y0, p->my, &p->sy);
 }
 
-// Whether the y sines, z recursion and y sines back run in one launch, a block per
-// plane: where two blocks fit a CU's LDS, so that few planes are not much serial work
-// each, or where there are enough planes for the card.  Solves in us, one launch
-// against three (sizes x, y, z): up to 64 KB FP64 32x32x32 17.9 / 23.3, FP32 96x96x128
-// 32.8 / 36.9; above, FP64 64x64x256 51.7 / 44.0, 128x64x192 56.9 / 52.5, 192x64x192
-// 69.6 / 76.0, 256x64x256 95 / 109, FP32 512x128x256 281 / 290.
-bool modal_plane(const pipe_plan_s* p) {
-    const size_t lds = plane_lds_bytes(p->sy, p->nz, p->rb);
-    return lds && (lds <= 64 * 1024 || p->sx.nm >= 160);
+// The axis (1: y, 2: x) whose sines run with the z sum in one launch, a block per plane
+// (0: none): where two blocks fit a CU's LDS, so that few planes are not much serial work
+// each, or where there are enough planes for the card; of two, that of fewer rows.
+// Solves in us, one launch against three (sizes x, y, z): up to 64 KB FP64 32x32x32 17.9
+// / 23.3, FP32 96x96x128 32.8 / 36.9; above, FP64 64x64x256 51.7 / 44.0, 128x64x192 56.9
+// / 52.5, 192x64x192 69.6 / 76.0, 256x64x256 95 / 109, FP32 512x128x256 281 / 290.
+int plane_axis(const pipe_plan_s* p) {
+    auto fits = [&](const SineAxis& rows, int planes) {
+        const size_t lds = plane_lds_bytes(rows, p->nz, p->rb);
+        return lds && (lds <= 64 * 1024 || planes >= 160);
+    };
+    const bool y = fits(p->sy, p->sx.nm), x = fits(p->sx, p->sy.nm);
+    return x && (!y || p->sx.na < p->sy.na) ? 2 : y ? 1 : 0;
+}
+
+// The same for a band of 8 hp8 distances, whose lines may be split: the axis and the
+// part with the least work of a block times the rounds of blocks (two a CU) that it
+// takes, in columns, plus 32 for what a block does once.
+int plane_split(const pipe_plan_s* p, int hp8, PlaneSplit* split) {
+    int axis = 0;
+    long best = 0;
+    for (int k = 1; k <= 2; ++k) {
+        const SineAxis& rows = k == 1 ? p->sy : p->sx;
+        const long planes = k == 1 ? p->sx.nm : p->sy.nm;
+        for (int parts = 1, w = p->nz; w > 0; ++parts) {
+            const bool whole = parts == 1;
+            const int hp = whole ? 0 : 8 * hp8, wl = w + 2 * hp;
+            const size_t lds = plane_lds_bytes(rows, wl, p->rb);
+            const long score = (planes * parts + 511) / 512 * (w + wl + 32L);
+            if (lds && lds <= 80 * 1024 && (!axis || score < best)) {
+                best = score;
+                axis = k;
+                *split = {w, hp};
+            }
+            const int next = ((p->nz + parts) / (parts + 1) + 7) / 8 * 8;      // parts + 1 parts
+            if (!whole && w == 8) break;
+            if (next < w || whole) w = next < p->nz ? next : 0;
+        }
+    }
+    return axis;
 }
 
 // How a sine-mode plan (p->sx, p->sy, p->band set) takes the z sum, and the size of its
-// table: directly where the band is short, else by recursion where a line folds at
-// most two modes per axis (up to 2N modes kept, the default) and the sum is whole,
-// else by a z convolution.
+// table: in a plane's launch where that is no more than kPlaneCycles of a SIMD; else
+// directly where the band is short, by recursion where the sum is whole and a line folds
+// at most four modes (2N modes per axis, the default), and by a z convolution.
+constexpr double kPlaneCycles = 24000.0;
 pipe_status_t choose_modal_z(pipe_plan_s* p) {
     const size_t lines = (size_t)p->sx.nm * p->sy.nm;
-    const int Nx = p->sx.na + 1, Ny = p->sy.na + 1;
-    p->nex = p->ney = p->znh = 0;
-    p->plane = false;
+    const int Nx = p->sx.na + 1, Ny = p->sy.na + 1, rz = p->band >= 0 ? p->band + 1 : p->nz;
+    p->plane = p->zdir = p->nexp = p->nex = p->znh = 0;
     p->nyq_elems = 0;
-    // modes folded per axis (a power of two; 0: more than four)
-    auto folds = [](int m, int N) { return m <= N ? 1 : m <= 2 * N ? 2 : m <= 4 * N ? 4 : 0; };
-    const int nex = folds(p->mx, Nx), ney = folds(p->my, Ny);
+    // modes folded onto a line's sines (0: more than 64, or no whole sum), in fours
+    const int nex = (p->mx - 1) / Nx + 1, ney = (p->my - 1) / Ny + 1;
+    const int folds = p->band < 0 && nex <= 64 && ney <= 64 / nex ? nex * ney : 0;
+    const int nexp = folds <= 2 ? folds : (folds + 3) / 4 * 4;
+    p->split = {p->nz, 0};
     if (modal_direct(p)) {
+        p->zdir = (rz + 6) / 8;
+        p->plane = plane_split(p, p->zdir, &p->split);
+    } else if (const int axis = plane_axis(p)) {
+        // 64-lane instructions (4 cycles) of a z sum, times the waves that a SIMD has
+        int lanes = 1;
+        while (8 * lanes < p->nz) lanes *= 2;
+        const int rows = axis == 1 ? p->sy.nm : p->sx.nm, waves = (rows * lanes + 63) / 64, zdir = (rz + 6) / 8;
+        const double simd = 4.0 * ((waves + 3) / 4), direct = 150.0 * zdir * simd,
+                     recursion = (nexp <= 2 ? 135.0 * nexp : 125.0 * nexp) * simd;
+        if (nexp && recursion <= direct && (nexp <= 4 || recursion <= kPlaneCycles)) {
+            p->plane = axis;
+            p->nexp = nexp;
+            p->nex = nex;
+        } else if (direct <= kPlaneCycles || (nexp && nexp <= 4)) {
+            p->plane = axis;
+            p->zdir = zdir;
+        }
+    }
+    if (p->plane) {
+        p->table_elems = plane_table_row(p->nexp, p->zdir) * lines;
+    } else if (modal_direct(p)) {
         p->table_elems = (size_t)(p->band + 1) * lines;
-    } else if (p->band < 0 && nex * ney > 0 && (nex * ney <= 4 || modal_plane(p))) {
+    } else if (nexp && nexp <= 4) {
+        p->nexp = nexp;
         p->nex = nex;
-        p->ney = ney;
-        p->plane = modal_plane(p);
-        p->table_elems = (1 + (size_t)nex * ney * kZexpEntries) * lines;
+        p->table_elems = (1 + (size_t)nexp * kZexpEntries) * lines;
     } else {
         p->znh = zconv_length(p->nz);
         if (p->znh < 0) return fail(PIPE_ERR_UNSUPPORTED_SIZE, "no z transform for nz = %d", p->nz);
@@ -604,11 +661,13 @@ pipe_status_t build_modal(pipe_plan_s* p, hipStream_t st, bool keep_green) {
     if (rs != PIPE_OK) return rs;
     HIP_TRY(dev_alloc(&p->table, p->table_elems * p->rb), "allocation (Green spectra)");
     Scratch s;
-    if (modal_direct(p))
-        HIP_TRY(launch_modal_band(p->table, p->rb, p->sx, p->sy, p->mx, p->my, planes, p->a, p->b, p->hz, igf, scale, st),
+    const bool zdirect = p->plane && !p->nexp;
+    if (zdirect || (!p->plane && modal_direct(p)))
+        HIP_TRY(launch_modal_band(p->table, p->rb, p->sx, p->sy, p->mx, p->my, planes, p->a, p->b, p->hz, igf, scale,
+                                  zdirect ? (int)plane_table_row(0, p->zdir) : planes, zdirect ? 7 : 0, st),
                 "mode factors");
-    else if (p->nex)
-        HIP_TRY(launch_modal_exp(p->table, p->rb, p->sx, p->sy, p->mx, p->my, p->nex, p->ney,
+    else if (p->nexp)
+        HIP_TRY(launch_modal_exp(p->table, p->rb, p->sx, p->sy, p->mx, p->my, p->nex, p->nexp,
                                  p->plane ? 8 : zexp_values(p->nz), p->a,
                                  p->b, p->hz, igf, scale, st),
                 "mode factors");
@@ -820,19 +879,30 @@ pipe_status_t run_modal_passes(pipe_plan_s* p, const void* rho, void* phi, void*
     char* B2 = B1 + m.b2_off;
     auto g = [&](int pass) { return args ? args + (size_t)pass * n : nullptr; };
     if (ev) HIP_TRY(hipEventRecord(ev[0], st), "event");
-    HIP_TRY(launch_sine<real>(p->sx, false, rho, B1, nz, nzp, nz, (long)ny * nz, nzp, m.p1, ny, vec_in, st, g(0), n),
-            "x sine transform");
-    if (ev) HIP_TRY(hipEventRecord(ev[1], st), "event");
     if (p->plane) {
-        HIP_TRY(launch_plane<real>(p->sy, p->sx.nm, B1, nz, nzp, p->nex * p->ney, p->table, st, g(1), n),
-                "y sine transforms and z recursion");
+        // the outer axis (slabs and rows of the user's arrays and of B1), the planes' axis
+        const bool xo = p->plane == 1;
+        const SineAxis &so = xo ? p->sx : p->sy, &si = xo ? p->sy : p->sx;
+        const long us = xo ? nz : (long)ny * nz, ur = xo ? (long)ny * nz : nz;
+        const long bs = xo ? nzp : m.p2, br = xo ? m.p1 : nzp;
+        HIP_TRY(launch_sine<real>(so, false, rho, B1, nz, nzp, us, ur, bs, br, si.n, vec_in, st, g(0), n),
+                "outer sine transform");
+        if (ev) HIP_TRY(hipEventRecord(ev[1], st), "event");
+        // parts of lines are read by their neighbours, so they go to the second array
+        char* O = p->split.w < nz ? B1 + align256((size_t)so.nm * si.n * nzp * p->rb) : B1;
+        HIP_TRY(launch_plane<real>(si, p->split, bs, br, so.nm, B1, O, nz, nzp, p->nexp, p->zdir, p->table, xo ? 1 : p->sy.nm,
+                                   xo ? p->sy.nm : 1, st, g(1), n),
+                "planes' sine transforms and z sum");
         if (ev)     // the two passes that this launch includes take no time of their own
             for (int i = 2; i < 5; ++i) HIP_TRY(hipEventRecord(ev[i], st), "event");
-        HIP_TRY(launch_sine<real>(p->sx, true, B1, phi, nz, nzp, nzp, m.p1, nz, (long)ny * nz, ny, vec_out, st, g(4), n),
-                "x sine transform back");
+        HIP_TRY(launch_sine<real>(so, true, O, phi, nz, nzp, bs, br, us, ur, si.n, vec_out, st, g(4), n),
+                "outer sine transform back");
         if (ev) HIP_TRY(hipEventRecord(ev[5], st), "event");
         return PIPE_OK;
     }
+    HIP_TRY(launch_sine<real>(p->sx, false, rho, B1, nz, nzp, nz, (long)ny * nz, nzp, m.p1, ny, vec_in, st, g(0), n),
+            "x sine transform");
+    if (ev) HIP_TRY(hipEventRecord(ev[1], st), "event");
     HIP_TRY(launch_sine<real>(p->sy, false, B1, B2, nz, nzp, m.p1, nzp, m.p2, nzp, p->sx.nm, true, st, g(1), n),
             "y sine transform");
     if (ev) HIP_TRY(hipEventRecord(ev[2], st), "event");
@@ -840,8 +910,8 @@ pipe_status_t run_modal_passes(pipe_plan_s* p, const void* rho, void* phi, void*
     if (modal_direct(p)) {      // never grouped: a banded batch member runs by itself
         HIP_TRY(launch_zband<real>(B2, B1 + m.b3_off, nzp, lines, p->band, p->table, st), "z sum");
         B2 = B1 + m.b3_off;
-    } else if (p->nex) {
-        HIP_TRY(launch_zexp<real>(B2, nzp, nz, lines, p->nex * p->ney, p->table, st, g(2), n), "z recursion");
+    } else if (p->nexp) {
+        HIP_TRY(launch_zexp<real>(B2, nzp, nz, lines, p->nexp, p->table, st, g(2), n), "z recursion");
     } else {
         HIP_TRY(launch_zconv<real>(p->znh, B2, nzp, nz, lines, p->table, p->ctx->tw, st, g(2), n), "z convolution");
     }
@@ -2043,7 +2113,7 @@ pipe_status_t pipe_batch_create(const pipe_plan_t* plans, int count, pipe_batch_
                 r->modal == p->modal &&
                 (!p->modal || (r->sx.na == p->sx.na && r->sx.nm == p->sx.nm && r->sy.na == p->sy.na &&
                                r->sy.nm == p->sy.nm &&    // the same sine matrices and z kernel
-                               r->nex == p->nex && r->ney == p->ney)))
+                               r->nex == p->nex && r->nexp == p->nexp && r->plane == p->plane && r->zdir == p->zdir)))
                 g = (int)k;
         }
         if (g < 0) {

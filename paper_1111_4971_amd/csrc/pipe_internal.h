@@ -235,30 +235,41 @@ inline int zexp_values(int n) { return n > 512 ? 16 : 8; }
 template <typename real>
 hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
                        const GroupArgs* group = nullptr, int ngroup = 1);
-// Table rows of launch_zexp and launch_plane; nex, ney (1, 2 or 4): modes folded per axis.
+// Table rows of launch_zexp and launch_plane: ne exponentials a line, of nex modes folded
+// in x times ne / nex or more in y; those past the last mode are zero.
 hipError_t launch_modal_exp(void* table, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int nex,
-                            int ney, int values, double a, double b, double hz, int igf, double scale, hipStream_t st);
-// M2 to M4 in one launch for planes (ny, nzp) that fit LDS: nplanes planes in place,
-// ne (1, 2, 4, 8 or 16) exponentials a line with 8 values a lane.  group entries: out
-// = the planes, table.
+                            int ne, int values, double a, double b, double hz, int igf, double scale, hipStream_t st);
+// M2 to M4 in one launch for planes that fit LDS: nplanes planes ps apart, of ax.n rows
+// rs apart, in place or to out; w < nz splits the lines of a direct z sum into parts of
+// w planes, each read with hp neighbours on both sides (then out != in).  The z sum by ne (1, 2 or a multiple of 4) exponentials a line
+// with 8 values a lane, or (ne = 0) directly over nb * 8 plane distances; a line's table
+// row is line_stride rows on, a plane's plane_stride.  group entries: out = the planes,
+// table.
 struct PlaneArgs {
-    void* data;
-    const void *table, *fwd, *inv;
-    int ny, na, h, he, no, ne, tm, nz, nzp, pitch, logp, ng;
+    const void *in, *table, *fwd, *inv;
+    void* out;
+    long rs, ps, tl, tp;
+    int n, na, h, he, no, ne, t, tm, nz, nzp, w, hp, wl, pitch, logp, ng;
 };
-// LDS bytes of a plane, 0 if it has more than 128 rows, lines of more than 512 values or
-// does not fit: rows an odd number of 128 bytes apart, so that the four rows of an
-// operand read fall on different banks.
-inline size_t plane_lds_bytes(const SineAxis& ay, int nz, int real_bytes) {
-    const int v = 16 / real_bytes, T = ((ay.na + 1) / 2 + 15) / 16;
+// LDS bytes of a plane, 0 if its lines have more than 512 values or it does not fit:
+// rows an odd number of 128 bytes apart, so that the four rows of an operand read fall
+// on different banks.
+struct PlaneSplit {
+    int w, hp;
+};
+inline size_t plane_lds_bytes(const SineAxis& ax, int nz, int real_bytes) {
+    const int v = 16 / real_bytes, T = ((ax.na + 1) / 2 + 15) / 16;
     size_t units = ((size_t)(nz + v - 1) / v * 16 + 127) / 128;
     units += units % 2 == 0;
     const size_t bytes = 2 * 16 * (size_t)T * units * 128;
-    return T <= 4 && nz <= 512 && bytes <= 160 * 1024 ? bytes : 0;
+    return nz <= 512 && bytes <= 160 * 1024 ? bytes : 0;
 }
+// Reals of a table row: exponentials, or the factor of distance 0, 7 unused, the others.
+inline size_t plane_table_row(int ne, int nb) { return ne ? 1 + (size_t)ne * kZexpEntries : 8 * ((size_t)nb + 1); }
 template <typename real>
-hipError_t launch_plane(const SineAxis& ay, int nplanes, void* data, int nz, int nzp, int ne, const void* table,
-                        hipStream_t s, const GroupArgs* group = nullptr, int ngroup = 1);
+hipError_t launch_plane(const SineAxis& ax, const PlaneSplit& split, long rs, long ps, int nplanes, const void* in,
+                        void* out, int nz, int nzp, int ne, int nb, const void* table, long line_stride,
+                        long plane_stride, hipStream_t s, const GroupArgs* group = nullptr, int ngroup = 1);
 // Sine matrices of one axis into frag (green.hip).
 hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStream_t st);
 // Folded z factors of mode lines [line0, line0 + nlines) (line = x mode * nmy + y
@@ -268,9 +279,10 @@ hipError_t launch_sine_frag(void* frag, int real_bytes, int na, int nm, hipStrea
 hipError_t launch_modal_factors(double* out, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz, int nh,
                                 double a, double b, double hz, int igf, double scale, long line0, long nlines,
                                 hipStream_t st);
-// The factors themselves at r < rz, rz values per mode line, in plan precision.
+// The factors themselves at r < rz, in plan precision: rows of pitch values per mode
+// line, distance 0 first, distance 1 at 1 + lead, zero beyond.
 hipError_t launch_modal_band(void* out, int real_bytes, const SineAxis& ax, const SineAxis& ay, int mx, int my, int rz,
-                             double a, double b, double hz, int igf, double scale, hipStream_t st);
+                             double a, double b, double hz, int igf, double scale, int pitch, int lead, hipStream_t st);
 // out_k = sum over |d| <= nb of table[line][|d|] in_{k+d} on nlines lines of nz
 // values, pitch apart (a multiple of a 16-byte vector; values beyond nz are zero in
 // the input and unspecified in the output); in != out, nb <= kModalBandMax.

@@ -110,6 +110,24 @@ def test_planes_match_the_padded_transform(torch_cuda, ny, zmax, nx, prec):
         p.close(), q.close()
 
 
+# thin meshes: planes of the shorter axis, many modes folded onto its lines (z sums
+# directly, by many exponentials, and by convolution where both are long), long axes
+@pytest.mark.parametrize("shape,modes", [((9, 96, 57), (192, 192)), ((254, 13, 32), (256, 256)), ((2, 200, 9), (80, 400)),
+                                         ((8, 246, 37), (256, 256)), ((5, 300, 20), (600, 600)), ((500, 6, 30), (10, 90)),
+                                         ((30, 17, 400), (500, 40)), ((12, 12, 300), (500, 500)), ((20, 11, 130), (30, 250)),
+                                         ((12, 90, 200), (400, 200)), ((400, 300, 4), (400, 300)), ((300, 310, 3), (310, 900))])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_thin_meshes_match_the_padded_transform(torch_cuda, shape, modes, prec):
+    for wall in ((False, True), (True, False)):
+        log("thin %s %s modes=%s wall=%s" % (prec, shape, modes, wall))
+        p, _ = _plan(shape, prec, wall, modes)
+        q, _ = _plan(shape, prec, wall, modes, padded=True)
+        rho = _rho(shape)
+        got, ref = gpu_solve(p, rho), gpu_solve(q, rho)
+        assert rel_l2(got, ref) <= 2 * TOL[prec] and rel_max(got, ref) <= 2 * TOL[prec], (shape, rel_l2(got, ref))
+        p.close(), q.close()
+
+
 # few modes (rectangular transforms), modes that fold once and several times
 @pytest.mark.parametrize("modes", [(1, 1), (3, 40), (20, 20), (39, 30), (40, 31), (200, 155)])
 @pytest.mark.parametrize("kind", [0, 1])
@@ -150,6 +168,24 @@ def test_banded_sums_match_eq18_oracle(torch_cuda, nb, shape, prec):
     padded = pipe.GreenPlan(*shape, hx, hy, hz, a, b, kind=kind, precision=prec, mx=mx, my=my, band=nb,
                             L=(plan.info.lx, plan.info.ly))
     assert torch_cuda.equal(plan.spectra(), padded.spectra())
+
+
+# lines split into parts, one plane over a part, parts that end with the line, planes of
+# x and of y, planes too large for one launch
+@pytest.mark.parametrize("shape", [(18, 16, 777), (49, 9, 437), (64, 130, 41), (128, 128, 129), (300, 260, 33), (7, 512, 100)])
+@pytest.mark.parametrize("nb", [0, 1, 8, 9, 16, 30])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_banded_parts_match_the_padded_transform(torch_cuda, nb, shape, prec):
+    from paper_1111_4971_amd import pipe
+    log("banded parts %s %s N=%d" % (prec, shape, nb))
+    plan, g = _plan(shape, prec, (True, False), (40, 50), band=nb)
+    hx, hy, hz, a, b, mx, my, kind = g
+    padded = pipe.GreenPlan(*shape, hx, hy, hz, a, b, kind=kind, precision=prec, mx=mx, my=my, band=nb,
+                            L=(plan.info.lx, plan.info.ly))
+    rho = _rho(shape)
+    got, ref = gpu_solve(plan, rho), gpu_solve(padded, rho)
+    assert rel_l2(got, ref) <= 2 * TOL[prec] and rel_max(got, ref) <= 2 * TOL[prec], rel_l2(got, ref)
+    plan.close(), padded.close()
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
