@@ -860,9 +860,9 @@ __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n
 // 0: the z sum directly, by a window of 8 values a lane and 8 distances a step (thin
 // meshes fold many modes: 9x96x57 FP32 with 40 exponentials a line 47 us by recursion).
 constexpr int kPlaneJobs = 3;      // 160 KB hold 40 jobs of 4 KB
-template <typename real, int NE>
+template <typename real, int KC, int NE>
 __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArgs* __restrict__ group) {
-    constexpr int V = 8 / sizeof(real), KC = 4;      // KC: 16-deep blocks of matrix rows in flight
+    constexpr int V = 8 / sizeof(real);
     using S = Sine<real, true, V, true>;
     using M = typename S::M;
     using vec = typename S::vec;
@@ -914,7 +914,7 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
 #pragma unroll
             for (int c = 0; c < V; ++c) sum[p][c] = acc_t{};
 #pragma unroll 1
-            for (int k0 = 0; k0 < kbn; k0 += KC) {
+            for (int k0 = 0; k0 < (KC == 4 ? kbn : 1); k0 += KC) {
                 veca af[KC][S::NA];
                 acc_t part[V];
                 __builtin_amdgcn_sched_barrier(0);       // no loads of the next parity before this
@@ -922,7 +922,7 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
                 for (int k = 0; k < KC; ++k)
 #pragma unroll
                     for (int q = 0; q < S::NA; ++q)
-                        if (k0 + k < kbn) af[k][q] = frag[(((p * nrt + rt) * kbn + k0 + k) * S::NA + q) * 64];
+                        af[k][q] = frag[(((p * nrt + rt) * kbn + min(k0 + k, kbn - 1)) * S::NA + q) * 64];
 #pragma unroll
                 for (int c = 0; c < V; ++c) part[c] = acc_t{};
 #pragma unroll
@@ -1120,9 +1120,8 @@ template <typename real> constexpr int sine_V(int kb) {
     return sizeof(real) == 4 ? (kb <= kSineBlocks ? 4 : 2) : (kb <= 4 ? 2 : 1);
 }
 
-template <typename real, bool INV, bool UV, int KB>
+template <typename real, bool INV, bool UV, int KB, int V>
 static hipError_t launch_sine_kb(SineArgs a, hipStream_t s, const GroupArgs* group, int ngroup) {
-    constexpr int V = sine_V<real>(KB);
     const int row_waves = a.rt > KB ? a.rt : KB;      // 4 row loads a thread and half
     // column groups per block: at least four waves while the tiles cover the chip
     a.g = 1;
@@ -1144,19 +1143,29 @@ static hipError_t launch_sine_kb(SineArgs a, hipStream_t s, const GroupArgs* gro
     return hipGetLastError();
 }
 
+template <typename real, bool INV, bool UV, bool NARROW>
+static hipError_t launch_sine_depth(SineArgs a, hipStream_t s, const GroupArgs* group, int ngroup) {
+    switch (a.kb) {
+#define X(KB_)                                                                                                \
+    case KB_: return launch_sine_kb<real, INV, UV, KB_, NARROW ? 1 : sine_V<real>(KB_)>(a, s, group, ngroup);
+        X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+#undef X
+    }
+    return hipErrorInvalidValue;
+}
 template <typename real, bool INV, bool UV>
 static hipError_t launch_sine_dir(SineArgs a, hipStream_t s, const GroupArgs* group, int ngroup) {
-    if (a.rt <= 8) {
-        switch (a.kb) {
-            case 1: return launch_sine_kb<real, INV, UV, 1>(a, s, group, ngroup);
-            case 2: return launch_sine_kb<real, INV, UV, 2>(a, s, group, ngroup);
-            case 3: return launch_sine_kb<real, INV, UV, 3>(a, s, group, ngroup);
-            case 4: return launch_sine_kb<real, INV, UV, 4>(a, s, group, ngroup);
-            case 5: return launch_sine_kb<real, INV, UV, 5>(a, s, group, ngroup);
-            case 6: return launch_sine_kb<real, INV, UV, 6>(a, s, group, ngroup);
-            case 7: return launch_sine_kb<real, INV, UV, 7>(a, s, group, ngroup);
-            case 8: return launch_sine_kb<real, INV, UV, 8>(a, s, group, ngroup);
+    if (a.rt <= 8 && a.kb <= kSineBlocks) {
+        // one column a lane where that still makes no more tiles than CUs: the products of
+        // a tile are one wave's serial work (solves, us: 247x17x47 FP32 44 -> 27, 104x19x85
+        // FP32 34.8 -> 29.4, 70x40x75 FP64 33.6 -> 30.6)
+        const int v = sine_V<real>(a.kb);
+        if (v > 1 && (a.ngroups * v + 15) / 16 * ngroup <= 256) {
+            a.wv *= v;
+            a.ngroups *= v;
+            return launch_sine_depth<real, INV, false, true>(a, s, group, ngroup);
         }
+        return launch_sine_depth<real, INV, UV, false>(a, s, group, ngroup);
     }
     // more than 256 rows on either side: half-width columns keep 2 x 16 kb rows in 64 KB
     constexpr int V = 8 / sizeof(real);
@@ -1314,18 +1323,20 @@ hipError_t launch_plane(const SineAxis& ax, const PlaneSplit& split, long rs, lo
     const int jobs = (wl + 16 * 8 / (int)sizeof(real) - 1) / (16 * 8 / (int)sizeof(real)) * a.t;
     if (jobs > 16 * kPlaneJobs) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nplanes, (unsigned)((nz + a.w - 1) / a.w), (unsigned)ngroup), block(64 * (jobs < 4 ? 4 : jobs > 16 ? 16 : jobs));
-    switch (per) {
-#define X(N_)                                                                                                \
-    case N_: {                                                                                               \
+    switch (per + 8 * (a.t < 4 ? a.t : 4)) {
+#define X(K_, N_)                                                                                            \
+    case N_ + 8 * K_: {                                                                                      \
         if (lds > 65536) {                                                                                   \
-            const hipError_t e = hipFuncSetAttribute((const void*)plane_kernel<real, N_>,                    \
+            const hipError_t e = hipFuncSetAttribute((const void*)plane_kernel<real, K_, N_>,                \
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);  \
             if (e != hipSuccess) return e;                                                                   \
         }                                                                                                    \
-        hipLaunchKernelGGL((plane_kernel<real, N_>), grid, block, lds, s, a, group);                         \
+        hipLaunchKernelGGL((plane_kernel<real, K_, N_>), grid, block, lds, s, a, group);                     \
         return hipGetLastError();                                                                            \
     }
-        X(0) X(1) X(2) X(4)
+#define Y(K_) X(K_, 0) X(K_, 1) X(K_, 2) X(K_, 4)
+        Y(1) Y(2) Y(3) Y(4)
+#undef Y
 #undef X
     }
     return hipErrorInvalidValue;

@@ -576,7 +576,10 @@ int plane_split(const pipe_plan_s* p, int hp8, PlaneSplit* split) {
 // How a sine-mode plan (p->sx, p->sy, p->band set) takes the z sum, and the size of its
 // table: in a plane's launch where that is no more than kPlaneCycles of a SIMD; else
 // directly where the band is short, by recursion where the sum is whole and a line folds
-// at most four modes (2N modes per axis, the default), and by a z convolution.
+// at most four modes (2N modes per axis, the default), eight in FP64, and by a z
+// convolution (us, convolution / recursion over eight: 256x128x1024 FP64 882 / 720, FP32
+// 398 / 379, 128x64x512 FP64 103.1 / 103.0, FP32 64.3 / 66.6; over 16 at 256x64x512 FP64
+// 199 / 235).
 constexpr double kPlaneCycles = 24000.0;
 pipe_status_t choose_modal_z(pipe_plan_s* p) {
     const size_t lines = (size_t)p->sx.nm * p->sy.nm;
@@ -611,7 +614,7 @@ pipe_status_t choose_modal_z(pipe_plan_s* p) {
         p->table_elems = plane_table_row(p->nexp, p->zdir) * lines;
     } else if (modal_direct(p)) {
         p->table_elems = (size_t)(p->band + 1) * lines;
-    } else if (nexp && nexp <= 4) {
+    } else if (nexp && nexp <= (p->rb == 8 ? 8 : 4)) {
         p->nexp = nexp;
         p->nex = nex;
         p->table_elems = (1 + (size_t)nexp * kZexpEntries) * lines;
