@@ -918,11 +918,19 @@ __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArg
                 veca af[KC][S::NA];
                 acc_t part[V];
                 __builtin_amdgcn_sched_barrier(0);       // no loads of the next parity before this
+                const gptr<const veca> fk = frag + ((p * nrt + rt) * kbn + k0) * S::NA * 64;
+                if (k0 + KC <= kbn) {
 #pragma unroll
-                for (int k = 0; k < KC; ++k)
+                    for (int k = 0; k < KC; ++k)
 #pragma unroll
-                    for (int q = 0; q < S::NA; ++q)
-                        af[k][q] = frag[(((p * nrt + rt) * kbn + min(k0 + k, kbn - 1)) * S::NA + q) * 64];
+                        for (int q = 0; q < S::NA; ++q) af[k][q] = fk[(k * S::NA + q) * 64];
+                } else {            // few modes, or the last blocks
+#pragma unroll
+                    for (int k = 0; k < KC; ++k)
+#pragma unroll
+                        for (int q = 0; q < S::NA; ++q)
+                            if (k0 + k < kbn) af[k][q] = fk[(k * S::NA + q) * 64];
+                }
 #pragma unroll
                 for (int c = 0; c < V; ++c) part[c] = acc_t{};
 #pragma unroll
