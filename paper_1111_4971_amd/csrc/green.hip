@@ -378,8 +378,9 @@ __global__ void modal_exp_kernel(T* out, ModalGeometry q, int nex, int ne, int v
     if (i >= nlines * ne) return;
     const int e = (int)(i % ne);
     const long line = i / ne;
-    T* row = out + line * (1 + ne * kZexpEntries);
-    T* o = row + 1 + e * kZexpEntries;
+    T* row = out + line * zexp_row(ne);
+    const int per = ne < 4 ? ne : 4;      // exponentials of a step: their entries side by side
+    T* o = row + kZexpLead + e / per * per * kZexpEntries + e % per;
     const int m1 = stored_mode((int)(line / q.nmy), (q.nmx + 1) / 2), n1 = stored_mode((int)(line % q.nmy), (q.nmy + 1) / 2);
     auto alias = [](int i, int m, int N) { return i % 2 ? (i + 1) * N - m : i * N + m; };
     const int m = alias(e % nex, m1, q.nax + 1), n = alias(e / nex, n1, q.nay + 1);
@@ -392,9 +393,9 @@ __global__ void modal_exp_kernel(T* out, ModalGeometry q, int nex, int ne, int v
         c = q.scale / kap * (q.igf ? igf_g(x, 1) : hi);
     }
     o[0] = (T)hi;
-    o[1] = sizeof(T) == 8 ? (T)lo : (T)(hi - (double)(T)hi + lo);
-    o[2] = (T)c;
-    for (int s = 0; s < 6; ++s) o[3 + s] = c == 0.0 ? (T)0 : (T)exp(-x * (double)(values << s));
+    o[per] = sizeof(T) == 8 ? (T)lo : (T)(hi - (double)(T)hi + lo);
+    o[2 * per] = (T)c;
+    for (int s = 0; s < 6; ++s) o[(3 + s) * per] = c == 0.0 ? (T)0 : (T)exp(-x * (double)(values << s));
     if (e == 0) row[0] = (T)modal_factor(q, line, 0);
 }
 

@@ -754,21 +754,22 @@ template <typename real> __device__ __forceinline__ real lane_shift(real x, int 
 }
 // The recursion sum of one line from a lane's values x; tl: the line's table row with
 // ng groups of NE exponentials; t: lane of the line, lane: of the wave.
-template <typename real, int V, int NE, typename Row>
-__device__ __forceinline__ void zexp_line(const real* x, real* o, Row tl, int ng, int logp, int t, int lane) {
-    constexpr int TE = kZexpEntries;
+template <typename real, int V, int NE>
+__device__ __forceinline__ void zexp_line(const real* x, real* o, gptr<const real> tl, int ng, int logp, int t, int lane) {
+    using ent = vecv<real, NE>;
     const int P = 1 << logp;
     const real c0 = tl[0];
 #pragma unroll
     for (int j = 0; j < V; ++j) o[j] = c0 * x[j];
     for (int q = 0; q < ng; ++q) {
-        const Row te = tl + 1 + q * NE * TE;
+        const auto te = reinterpret_cast<gptr<const ent>>(tl + kZexpLead + q * NE * kZexpEntries);
+        const ent vh = te[0], vl = te[1], vc = te[2];
         real rh[NE], rl[NE], f[NE], g[NE];
         auto step = [&](int e, real y, real xv) { return fma(rh[e], y, fma(rl[e], y, xv)); };
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            rh[e] = te[e * TE];
-            rl[e] = te[1 + e * TE];
+            rh[e] = velem<real, NE>(vh, e);
+            rl[e] = velem<real, NE>(vl, e);
             real s = 0, b = 0;
 #pragma unroll
             for (int j = 0; j < V; ++j) {
@@ -782,16 +783,17 @@ __device__ __forceinline__ void zexp_line(const real* x, real* o, Row tl, int ng
         for (int s = 0; s < 6; ++s) {
             if (s >= logp) break;
             const int d = 1 << s;
+            const ent vw = te[3 + s];
 #pragma unroll
             for (int e = 0; e < NE; ++e) {
-                const real w = te[3 + e * TE + s];
+                const real w = velem<real, NE>(vw, e);
                 f[e] = fma(w, lane_shift(f[e], (lane - d) * 4, t >= d), f[e]);
                 g[e] = fma(w, lane_shift(g[e], (lane + d) * 4, t + d < P), g[e]);
             }
         }
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            const real c = te[2 + e * TE];
+            const real c = velem<real, NE>(vc, e);
             real y = f[e], z = g[e];
 #pragma unroll
             for (int j = 0; j < V; ++j) {
@@ -828,6 +830,7 @@ __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n
         table = (const real*)group[blockIdx.z].table;
     }
     if constexpr (WAVE) logp = 6;
+    if constexpr (sizeof(real) == 4) ng = 1;
     const int P = 1 << logp, t = threadIdx.x & (P - 1), lane = threadIdx.x & 63;
     const long line = (long)blockIdx.x * (256 >> logp) + (threadIdx.x >> logp);
     const bool active = line < nlines;
@@ -835,7 +838,7 @@ __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n
     const gptr<real> row = to_global(data) + at * pitch;
     real x[V], o[V];
     zexp_load<real, V>(x, row, t * V, n);
-    zexp_line<real, V, NE>(x, o, to_global(table) + at * (1 + ng * NE * kZexpEntries), ng, logp, t, lane);
+    zexp_line<real, V, NE>(x, o, to_global(table) + at * zexp_row(ng * NE), ng, logp, t, lane);
     if (!active) return;
 #pragma unroll
     for (int q = 0; q < NV; ++q) {

@@ -617,7 +617,7 @@ pipe_status_t choose_modal_z(pipe_plan_s* p) {
     } else if (nexp && nexp <= (p->rb == 8 ? 8 : 4)) {
         p->nexp = nexp;
         p->nex = nex;
-        p->table_elems = (1 + (size_t)nexp * kZexpEntries) * lines;
+        p->table_elems = plane_table_row(nexp, 0) * lines;
     } else {
         p->znh = zconv_length(p->nz);
         if (p->znh < 0) return fail(PIPE_ERR_UNSUPPORTED_SIZE, "no z transform for nz = %d", p->nz);

@@ -231,6 +231,8 @@ hipError_t launch_zconv(int nh, void* data, long pitch, int n, long nlines, cons
 // rows of 1 + ne kZexpEntries values, W(0) and per exponential r hi, r lo, C, r^{V
 // 2^s} for s < 6, V = zexp_values(n) the values of a lane.
 constexpr int kZexpEntries = 9;
+constexpr int kZexpLead = 4;
+constexpr __host__ __device__ int zexp_row(int ne) { return kZexpLead + ne * kZexpEntries; }
 inline int zexp_values(int n) { return n > 512 ? 16 : 8; }
 template <typename real>
 hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
@@ -265,7 +267,7 @@ inline size_t plane_lds_bytes(const SineAxis& ax, int nz, int real_bytes) {
     return nz <= 512 && bytes <= 160 * 1024 ? bytes : 0;
 }
 // Reals of a table row: exponentials, or the factor of distance 0, 7 unused, the others.
-inline size_t plane_table_row(int ne, int nb) { return ne ? 1 + (size_t)ne * kZexpEntries : 8 * ((size_t)nb + 1); }
+inline size_t plane_table_row(int ne, int nb) { return ne ? zexp_row(ne) : 8 * (nb + 1); }
 template <typename real>
 hipError_t launch_plane(const SineAxis& ax, const PlaneSplit& split, long rs, long ps, int nplanes, const void* in,
                         void* out, int nz, int nzp, int ne, int nb, const void* table, long line_stride,
