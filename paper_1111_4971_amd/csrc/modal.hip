@@ -11,12 +11,13 @@
 //   M3 z sum of every mode line with its folded z factor, in place: a recursion
 //      while few modes fold onto a line [zexp], else a convolution (real lines
 //      zero-padded, one real spectrum per line) [zconv]; banded plans a filter [zband]
-//   M4 y sine transform back, M5 x sine transform back to (nx, ny, nz),
-// with nothing padded in x and y: 10 n values move instead of the 35 n of the
+//   M4 y sine transform back, M5 x sine transform back to (nx, ny, nz);
+// where the planes of one axis fit LDS, M2 to M4 are one launch [plane] and the
+// longer axis goes first and last.  Nothing is padded in x and y: 10 n values move instead of the 35 n of the
 // padded transform (n = nx ny nz, the spectra included).  nzp is nz rounded up
 // to a 16-byte vector.  Whole solves, padded transform -> sine modes: 128x128x512
-// FP32 235 -> 103 us, FP64 456 -> 160 us; 256x256x1024 FP32 1853 -> 765 us;
-// 64x64x256 FP64 74 -> 39 us; errors against 64 bits no larger (FP32 1.4e-7
+// FP32 235 -> 103 us, FP64 456 -> 162 us; 256x256x1024 FP32 1853 -> 768 us;
+// 64x64x256 FP64 74 -> 40 us; 32x32x32 FP64 30 -> 19 us; errors against 64 bits no larger (FP32 1.4e-7
 // against 2.2e-7).
 #include <algorithm>
 
@@ -734,7 +735,7 @@ void zconv_kernel(real* data, long pitch, int n, long nlines, const cplx<real>* 
 // The z factor of every mode is an exponential beyond the first plane, W(d) = C
 // r^{d-1} for d >= 1 with r = e^{-kappa hz} (Eq. 9 as it stands, Eq. 15 with its
 // constant factor), and a mode line folds at most 2 x 2 of them while no more than
-// 2N modes are kept per axis.  The z convolution is then
+// 2N modes are kept per axis (beyond, in steps of four).  The z convolution is then
 //   out_k = W(0) x_k + sum_e C_e (F_k + G_k),
 //   F_{k+1} = r F_k + x_k,  G_{k-1} = r G_k + x_k:
 // no transform, no padding and no spectra to read (2 n values move instead of 3 n).
@@ -745,9 +746,11 @@ void zconv_kernel(real* data, long pitch, int n, long nlines, const cplx<real>* 
 // carries (FP32 errors up to 4x the transform's at kappa hz = 0.05; with it at most
 // 0.94x over kappa hz = 1e-4 .. 2).
 //
-// Measured: 16384 lines of 512, four exponentials, FP32 20 us (the z convolution 27),
-// FP64 43 us (60); 65536 lines of 1024, one exponential, FP32 125 us (236; a copy of
-// the lines takes 110).  16 values a lane instead of 8 up to 512: 22 and 54 us.
+// Measured: 16384 lines of 512, four exponentials, FP32 21 us (the z convolution 27),
+// FP64 40 us (60); 65536 lines of 1024, one exponential, FP32 123 us (236; a copy of
+// the lines takes 110).  16 values a lane instead of 8 up to 512: 22 and 54 us.  The
+// entries of a step's exponentials lie side by side, one vector load each: 27 x 9216
+// lines of 192 FP32 191 -> 163 us.
 template <typename real> __device__ __forceinline__ real lane_shift(real x, int idx, bool in) {
     const real v = from_lane(x, idx);
     return in ? v : (real)0;
@@ -854,14 +857,15 @@ __global__ __launch_bounds__(256) void zexp_kernel(real* data, long pitch, int n
 // M2 to M4 in one block for one mode of the outer axis, where a plane (rows of the
 // other axis, nz) fits LDS: its sines, the z sum of its mode lines and its sines back,
 // with the plane read and written once (6 n values less traffic) and three launches a
-// solve instead of five.  Bound by the serial work of one block per plane (one product,
-// the z sum, one product: 128x32 FP32 rows take 11 us against 18 for three launches);
-// with a wave taking all rows of its columns, lines of 32 left three of four waves idle
-// (40 us a 128x128x32 solve, now 26).  A wave's job is 16 rows of both parities in 16 V
-// columns; the forward product is in place, so its sums (kPlaneJobs a wave at most)
-// stay in registers until all waves have read.  NE: exponentials of a recursion step,
-// 0: the z sum directly, by a window of 8 values a lane and 8 distances a step (thin
-// meshes fold many modes: 9x96x57 FP32 with 40 exponentials a line 47 us by recursion).
+// solve instead of five.  Bound by the serial work of one block per plane: one product,
+// the z sum, one product (32x32x32 FP64 6.7 us, 70x40x75 FP64 17).  A wave's job is 16
+// rows of both parities in 16 V columns; with a wave taking all rows of its columns,
+// lines of 32 left three of four waves idle (a 128x128x32 FP32 solve 40 us, now 26; in
+// five launches 34).  The forward product is in place, so its sums (kPlaneJobs a wave at
+// most) stay in registers until all waves have read.  KC: 16-deep blocks of matrix rows
+// in flight.  NE: exponentials of a recursion step, 0: the z sum directly, by a window
+// of 8 values a lane and 8 distances a step, where a recursion over many folded modes
+// costs more (9x96x57 FP32, 40 exponentials a line: 47 us, 31 by the padded transforms).
 constexpr int kPlaneJobs = 3;      // 160 KB hold 40 jobs of 4 KB
 template <typename real, int KC, int NE>
 __global__ __launch_bounds__(1024) void plane_kernel(PlaneArgs a, const GroupArgs* __restrict__ group) {
@@ -1290,8 +1294,10 @@ template <typename real>
 hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
                        const GroupArgs* group, int ngroup) {
     if (nlines <= 0 || n < 1 || n > 1024 || pitch < n || pitch % (16 / (int)sizeof(real))) return hipErrorInvalidValue;
-    return zexp_values(n) == 16 ? launch_zexp_v<real, 16>(data, pitch, n, nlines, ne, table, s, group, ngroup)
-                                : launch_zexp_v<real, 8>(data, pitch, n, nlines, ne, table, s, group, ngroup);
+    const int v = zexp_values(n, (int)sizeof(real));
+    return v == 16   ? launch_zexp_v<real, 16>(data, pitch, n, nlines, ne, table, s, group, ngroup)
+           : v == 12 ? launch_zexp_v<real, 12>(data, pitch, n, nlines, ne, table, s, group, ngroup)
+                     : launch_zexp_v<real, 8>(data, pitch, n, nlines, ne, table, s, group, ngroup);
 }
 
 template <typename real>

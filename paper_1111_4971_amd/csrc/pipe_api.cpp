@@ -671,7 +671,7 @@ pipe_status_t build_modal(pipe_plan_s* p, hipStream_t st, bool keep_green) {
                 "mode factors");
     else if (p->nexp)
         HIP_TRY(launch_modal_exp(p->table, p->rb, p->sx, p->sy, p->mx, p->my, p->nex, p->nexp,
-                                 p->plane ? 8 : zexp_values(p->nz), p->a,
+                                 p->plane ? 8 : zexp_values(p->nz, p->rb), p->a,
                                  p->b, p->hz, igf, scale, st),
                 "mode factors");
     else if ((rs = build_modal_spectra(p, planes, igf, scale, s, st)) != PIPE_OK)

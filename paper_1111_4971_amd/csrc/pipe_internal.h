@@ -227,13 +227,23 @@ inline int zconv_length(int n) {
 template <typename real>
 hipError_t launch_zconv(int nh, void* data, long pitch, int n, long nlines, const void* table, const TwiddleBank& tw,
                         hipStream_t s, const GroupArgs* group = nullptr, int ngroup = 1);
-// The same by recursion for lines of ne (1, 2 or 4) exponentials (n <= 1024): table
-// rows of 1 + ne kZexpEntries values, W(0) and per exponential r hi, r lo, C, r^{V
-// 2^s} for s < 6, V = zexp_values(n) the values of a lane.
-constexpr int kZexpEntries = 9;
-constexpr int kZexpLead = 4;
+// The same by recursion for lines of ne (1, 2 or a multiple of 4) exponentials (n <=
+// 1024): table rows of zexp_row(ne) values, W(0), 3 unused, and per step of 4 (ne)
+// exponentials theirs of r hi, r lo, C, r^{V 2^s} for s < 6, V = zexp_values(n) the
+// values of a lane.
+constexpr int kZexpEntries = 9, kZexpLead = 4;
 constexpr __host__ __device__ int zexp_row(int ne) { return kZexpLead + ne * kZexpEntries; }
-inline int zexp_values(int n) { return n > 512 ? 16 : 8; }
+// 8, or 12 where 12 values on a power of two of lanes leave fewer of them idle and the
+// registers allow it, 16 beyond 768 (solves in us, 8 or 16 / 12 values: FP32 128x128x300
+// 85.0 / 79.7, x192 58 / 57, 140x140x768 229 / 221, FP64 424 / 415; FP64 128x128x384
+// 128 / 132, FP32 130x130x90 55.1 / 55.5).
+inline int zexp_values(int n, int real_bytes) {
+    if (n > 512) return n > 768 ? 16 : 12;
+    int a = 8, b = 12;
+    while (a < n) a *= 2;
+    while (b < n) b *= 2;
+    return real_bytes == 4 && n > 96 && b < a ? 12 : 8;
+}
 template <typename real>
 hipError_t launch_zexp(void* data, long pitch, int n, long nlines, int ne, const void* table, hipStream_t s,
                        const GroupArgs* group = nullptr, int ngroup = 1);
