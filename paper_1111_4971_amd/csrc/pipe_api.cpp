@@ -548,7 +548,11 @@ int plane_axis(const pipe_plan_s* p) {
 
 // The same for a band of 8 hp8 distances, whose lines may be split: the axis and the
 // part with the least work of a block times the rounds of blocks (two a CU) that it
-// takes, in columns, plus 32 for what a block does once.
+// takes, in columns, plus 32 for what a block does once.  Parts that read neighbours only
+// on small meshes, else the launches of their own (us, one launch / three, N = 2 FP32:
+// 64x64x256 26.1 / 29.8, 128x128x64 34.4 / 36.9, 128x128x256 61.5 / 56.9, 256x64x1024
+// 282 / 173; N = 12 FP64: 32x32x128 20.3 / 24.4, 64x64x64 28.2 / 24.6; without neighbours,
+// N = 0 FP32: 32x32x128 18.9 / 24.0, 256x64x1024 158 / 170).
 int plane_split(const pipe_plan_s* p, int hp8, PlaneSplit* split) {
     int axis = 0;
     long best = 0;
@@ -560,7 +564,8 @@ int plane_split(const pipe_plan_s* p, int hp8, PlaneSplit* split) {
             const int hp = whole ? 0 : 8 * hp8, wl = w + 2 * hp;
             const size_t lds = plane_lds_bytes(rows, wl, p->rb);
             const long score = (planes * parts + 511) / 512 * (w + wl + 32L);
-            if (lds && lds <= 80 * 1024 && (!axis || score < best)) {
+            const bool small = planes * rows.na * p->nz <= (hp <= 8 ? 1L << 20 : 1L << 17);
+            if (lds && lds <= 80 * 1024 && (!hp || small) && (!axis || score < best)) {
                 best = score;
                 axis = k;
                 *split = {w, hp};
