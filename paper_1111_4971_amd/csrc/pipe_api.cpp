@@ -1704,7 +1704,15 @@ pipe_status_t pipe_green_plan_banded(int nx, int ny, int nz, double hx, double h
     p->tile = band_tile(lx, p->rb);
     // Sine modes as for the 3-D plans; a forced x-pass kernel or tile and a kept Green
     // table (made on the way to the padded transform's coefficients) ask for the latter.
-    if (own_lengths && !keep && !getenv("PIPE_BAND_KERNEL") && !getenv("PIPE_BAND_TILE0") && modal_mesh(p)) {
+    // So does N = 0 (three padded passes, no window) on meshes that it hardly pads and whose
+    // sine products are long, W = the modes of both axes (us, padded / sine modes: FP32
+    // 256x256x256 192 / 208, 512x512x64 261 / 395, W = 382 138 / 141, W = 254 84 / 84; FP64
+    // 357 / 412, 591 / 870, W = 382 310 / 226; padded by half, 300x300x256 521 / 470).
+    auto padded0 = [&] {
+        return nband == 0 && (double)lx * ly <= 4.3 * nx * ny && p->sx.nm + p->sy.nm >= (p->rb == 4 ? 380 : 480);
+    };
+    if (own_lengths && !keep && !getenv("PIPE_BAND_KERNEL") && !getenv("PIPE_BAND_TILE0") && modal_mesh(p) &&
+        !padded0()) {
         p->modal = true;
         p->band = std::min(nband, nz - 1);
         if (nband < 0) {

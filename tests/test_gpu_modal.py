@@ -188,6 +188,21 @@ def test_banded_parts_match_the_padded_transform(torch_cuda, nb, shape, prec):
     plan.close(), padded.close()
 
 
+# one plane kept on large meshes: the padded passes where they hardly pad, else sine modes
+@pytest.mark.parametrize("n,nb,padded_route", [(256, 0, True), (256, 1, False), (220, 0, False), (100, 0, False)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_one_plane_route(torch_cuda, n, nb, padded_route, prec):
+    from paper_1111_4971_amd import pipe
+    log("one plane %s n=%d N=%d" % (prec, n, nb))
+    g = (A / n, B / n, HZ, A, B)
+    p = pipe.GreenPlan(n, n, 6, *g, precision=prec, mx=2 * n, my=2 * n, band=nb)
+    q = pipe.GreenPlan(n, n, 6, *g, precision=prec, mx=2 * n, my=2 * n, band=nb, L=(p.info.lx, p.info.ly))
+    rho = _rho((n, n, 6))
+    got, ref = gpu_solve(p, rho), gpu_solve(q, rho)
+    assert np.array_equal(got, ref) == padded_route
+    assert rel_l2(got, ref) <= 2 * TOL[prec] and rel_max(got, ref) <= 2 * TOL[prec], rel_l2(got, ref)
+
+
 @pytest.mark.parametrize("prec", ["fp64", "fp32"])
 def test_route_follows_the_geometry(torch_cuda, prec):
     """Off the lattice (spacing, offset) or with lengths of its own a mesh keeps the
