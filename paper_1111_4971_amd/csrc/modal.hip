@@ -1171,11 +1171,13 @@ static hipError_t launch_sine_depth(SineArgs a, hipStream_t s, const GroupArgs* 
 template <typename real, bool INV, bool UV>
 static hipError_t launch_sine_dir(SineArgs a, hipStream_t s, const GroupArgs* group, int ngroup) {
     if (a.rt <= 8 && a.kb <= kSineBlocks) {
-        // one column a lane where that still makes no more tiles than CUs: the products of
-        // a tile are one wave's serial work (solves, us: 247x17x47 FP32 44 -> 27, 104x19x85
-        // FP32 34.8 -> 29.4, 70x40x75 FP64 33.6 -> 30.6)
-        const int v = sine_V<real>(a.kb);
-        if (v > 1 && (a.ngroups * v + 15) / 16 * ngroup <= 256) {
+        // one column a lane where that makes few tiles: the products of a tile are one wave's
+        // serial work, a block's matrix rows the price (solves, us: 247x17x47 FP32 44 -> 27,
+        // 104x19x85 FP32 34.8 -> 29.4, 70x40x75 FP64 33.6 -> 30.6; up to 512 tiles 250x100x60
+        // FP32 50.9 -> 45.0, 120x120x60 FP64 44.7 -> 46.1; up to 1024 64x64x256 FP64 44.5 ->
+        // 40.9, FP32 30.8 -> 28.1, 160x160x64 FP32 47.0 -> 50.4)
+        const int v = sine_V<real>(a.kb), few = a.kb <= 2 ? 1024 : sizeof(real) == 4 ? 512 : 256;
+        if (v > 1 && (a.ngroups * v + 15) / 16 * ngroup <= few) {
             a.wv *= v;
             a.ngroups *= v;
             return launch_sine_depth<real, INV, false, true>(a, s, group, ngroup);
