@@ -141,8 +141,9 @@ pipe_status_t pipe_green_plan(int nx, int ny, int nz, double hx, double hy, doub
  * the four terms are one real factor per mode and nothing is padded in x and y:
  * the same potential to rounding, in about a third of the memory traffic.  Such
  * a plan reports the lengths and workspace the padded transform would have, and
- * 0 for the launch schedule (xtile, apad, zblocks, xnt, a1pad); explicit lengths
- * or a forced PIPE_SCHEDULE keep the padded transform.  hip_stream (a hipStream_t, may be NULL) orders the plan build's GPU
+ * 0 for the launch schedule (xtile, apad, zblocks, xnt, a1pad); explicit lengths,
+ * lengths to be tuned (PIPE_AUTOTUNE*) or a forced PIPE_SCHEDULE keep the padded
+ * transform.  hip_stream (a hipStream_t, may be NULL) orders the plan build's GPU
  * work; the call still returns only when the build has finished.
  * Every other 3-D plan (here, pipe_green_plan_region, pipe_free_plan) also picks a
  * launch schedule by timing the solve on scratch buffers during the build:
@@ -174,7 +175,8 @@ pipe_status_t pipe_green_plan(int nx, int ny, int nz, double hx, double hy, doub
  * "pipe-tune-v2 arch nx ny nz real_bytes nval members lx ly lz"; nval is 9 for
  * pipe plans and 1 for free-space plans, members 1 or 16).  An entry whose
  * lengths this mesh cannot use (see the rules above) is ignored and the
- * lengths are tuned again; malformed lines are skipped.
+ * lengths are tuned again; malformed lines are skipped.  A mesh on the pipe's
+ * lattice solves faster untuned, in the sine modes (above).
  */
 pipe_status_t pipe_green_plan_ex(int nx, int ny, int nz, double hx, double hy, double hz,
                                  double a, double b, int kind, int mx, int my,

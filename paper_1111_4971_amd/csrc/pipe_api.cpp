@@ -1517,10 +1517,10 @@ pipe_status_t create_plan(int nx, int ny, int nz, double hx, double hy, double h
     p->device = dev; p->ctx = ctx;
     p->nval = free_space ? 1 : 9;
     // Sine modes where the mesh fills the pipe's lattice in x and y and the caller
-    // left the algorithm open: explicit padded lengths or a forced schedule ask
-    // for the padded transform.
+    // left the algorithm open: explicit or tuned padded lengths or a forced schedule
+    // ask for the padded transform.
     const char* sched = getenv("PIPE_SCHEDULE");
-    if (!free_space && own_lengths && (!sched || !strcmp(sched, "fixed")) && modal_mesh(p)) {
+    if (!free_space && own_lengths && !tune && (!sched || !strcmp(sched, "fixed")) && modal_mesh(p)) {
         p->modal = true;
         p->tile = xprod_tile(lx, p->rb);
         p->a1pad = a1_pad_rule(p);
@@ -1530,7 +1530,6 @@ pipe_status_t create_plan(int nx, int ny, int nz, double hx, double hy, double h
             return s;
         }
         p->ws_bytes = plan_ws_bytes(p);
-        p->tune_ms = tune_ms;
         p->build_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         reg_add(p);
         *out = p;

@@ -88,3 +88,21 @@ def test_bad_cache_entries_are_tuned_again(tmp_path):
         tol = 1e-12 if prec == "fp64" else 1e-5
         assert rel_l2(got, ref) <= tol and rel_max(got, ref) <= tol
     os.environ.pop("PIPE_TUNE_CACHE", None)
+
+
+@pytest.mark.parametrize("mode", [True, "batch"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_tuned_plan_solves_at_its_lengths(mode, prec, monkeypatch):
+    """On the pipe's lattice too: the bits of a plan made with the tuned lengths."""
+    import torch
+    from paper_1111_4971_amd import pipe
+    monkeypatch.delenv("PIPE_TUNE_CACHE", raising=False)
+    nx, ny, nz = 26, 22, 34
+    g = (1.0 / (nx + 1), 1.2 / (ny + 1), 0.06, 1.0, 1.2)
+    log("autotune on the lattice: %s %s" % (prec, mode))
+    tuned = pipe.GreenPlan(nx, ny, nz, *g, precision=prec, autotune=mode)
+    i = tuned.info
+    same = pipe.GreenPlan(nx, ny, nz, *g, precision=prec, L=(i.lx, i.ly, i.lz))
+    assert i.tune_ms > 0 and i.xtile != 0
+    x = torch.from_numpy(np.random.default_rng(8).standard_normal((nx, ny, nz))).to("cuda", tuned.dtype)
+    assert torch.equal(tuned.solve(x), same.solve(x))
