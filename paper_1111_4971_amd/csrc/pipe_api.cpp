@@ -1907,10 +1907,8 @@ pipe_status_t pipe_plan_green_table(pipe_plan_t p, void* out, void* stream) {
     return PIPE_OK;
 }
 
-pipe_status_t pipe_plan_spectra(pipe_plan_t p, void* out, void* stream) {
-    if (!reg_has(p)) return fail(PIPE_ERR_INVALID_ARG, "invalid or destroyed plan handle");
-    if (!out) return fail(PIPE_ERR_INVALID_ARG, "out must be non-null");
-    hipStream_t st = (hipStream_t)stream;
+namespace {
+pipe_status_t copy_spectra(const pipe_plan_s* p, void* out, hipStream_t st) {
     if (p->band >= 0 && !p->modal) {
         HIP_TRY(hipMemcpyAsync(out, p->table, p->table_elems * p->rb, hipMemcpyDeviceToDevice, st), "spectra copy");
     } else if (p->modal) {
@@ -1947,6 +1945,18 @@ pipe_status_t pipe_plan_spectra(pipe_plan_t p, void* out, void* stream) {
     }
     HIP_TRY(hipStreamSynchronize(st), "spectra copy");
     return PIPE_OK;
+}
+}  // namespace
+
+pipe_status_t pipe_plan_spectra(pipe_plan_t p, void* out, void* stream) {
+    if (!reg_has(p)) return fail(PIPE_ERR_INVALID_ARG, "invalid or destroyed plan handle");
+    if (!out) return fail(PIPE_ERR_INVALID_ARG, "out must be non-null");
+    int cur = -1;
+    HIP_TRY(hipGetDevice(&cur), "hipGetDevice");
+    if (cur != p->device) HIP_TRY(hipSetDevice(p->device), "hipSetDevice");
+    const pipe_status_t s = copy_spectra(p, out, (hipStream_t)stream);
+    if (cur != p->device) (void)hipSetDevice(cur);
+    return s;
 }
 
 pipe_status_t pipe_fft3d(int real_bytes, int n0, int n1, int n2, const char* dirs, const void* in, void* out,

@@ -103,3 +103,30 @@ for flag in (pipe.AUTOTUNE, pipe.AUTOTUNE_BATCH):
     assert info(h).tune_ms > 0
     assert info(h).xtile != 0 and solve_kernels(h) == PADDED
 """)
+
+
+def test_spectra_are_built_on_the_plans_device(run):
+    """pipe_plan_spectra of a sine-mode plan, called with another device current."""
+    run("""
+out = ctypes.c_void_p(1 << 20)
+L = pipe.lib()
+for band in (None, 2):
+    fake.hipSetDevice(1)
+    h = plan((9, 8, 12))
+    if band is not None:
+        pipe.check(L.pipe_green_plan_banded(9, 8, 12, .1, 1 / 9, .05, 1., 1., 0., 0., pipe.PREC_FP32 | 1, 18, 16, 0, 0,
+                                            band, 0., None, ctypes.byref(h)))
+    assert info(h).xtile == 0
+    fake.hipSetDevice(0)
+    calls()
+    if band is None:
+        pipe.check(L.pipe_plan_spectra(h, out, None))
+    else:
+        copy = ctypes.create_string_buffer(1 << 22)
+        pipe.check(L.pipe_plan_spectra(h, copy, None))
+    seen = calls()
+    assert seen[1, "malloc"] > 0 and {d for d, _ in seen} == {1}, seen
+    now = ctypes.c_int(-1)
+    fake.hipGetDevice(ctypes.byref(now))
+    assert now.value == 0
+""")
