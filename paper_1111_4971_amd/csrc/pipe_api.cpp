@@ -531,6 +531,14 @@ bool modal_mesh(pipe_plan_s* p) {
            lattice_axis(p->ny, p->hy, p->b, p->y0, p->my, &p->sy);
 }
 
+// Whether a 3-D pipe plan with its lengths left open is solved in the sine modes: where
+// the mesh allows it, unless a forced schedule (or explicit or tuned padded lengths, which
+// the callers look at) asks for the padded transform.
+bool default_modal(pipe_plan_s* p) {
+    const char* sched = getenv("PIPE_SCHEDULE");
+    return (!sched || !strcmp(sched, "fixed")) && modal_mesh(p);
+}
+
 // The axis (1: y, 2: x) whose sines run with the z sum in one launch, a block per plane
 // (0: none): where two blocks fit a CU's LDS, so that few planes are not much serial work
 // each, or where there are enough planes for the card; of two, that of fewer rows.
@@ -1516,11 +1524,7 @@ pipe_status_t create_plan(int nx, int ny, int nz, double hx, double hy, double h
     p->x0 = x0; p->y0 = y0; p->g0 = g0;
     p->device = dev; p->ctx = ctx;
     p->nval = free_space ? 1 : 9;
-    // Sine modes where the mesh fills the pipe's lattice in x and y and the caller
-    // left the algorithm open: explicit or tuned padded lengths or a forced schedule
-    // ask for the padded transform.
-    const char* sched = getenv("PIPE_SCHEDULE");
-    if (!free_space && own_lengths && !tune && (!sched || !strcmp(sched, "fixed")) && modal_mesh(p)) {
+    if (!free_space && own_lengths && !tune && default_modal(p)) {
         p->modal = true;
         p->tile = xprod_tile(lx, p->rb);
         p->a1pad = a1_pad_rule(p);
@@ -1639,7 +1643,7 @@ pipe_status_t time_full_for(const pipe_plan_s* b, hipStream_t st, double* ms_out
     q.hx = b->hx; q.hy = b->hy; q.hz = b->hz; q.a = b->a; q.b = b->b; q.x0 = b->x0; q.y0 = b->y0;
     q.device = b->device; q.ctx = b->ctx; q.nval = 9;
     q.tile = xprod_tile(lx, q.rb); q.apad = 0; q.zcap = 2048;
-    if (modal_mesh(&q)) {
+    if (default_modal(&q)) {
         // its matrices, and a table of zeros of the right size
         q.modal = true;
         if ((s = choose_modal_z(&q)) != PIPE_OK) return s;

@@ -130,3 +130,16 @@ for band in (None, 2):
     fake.hipGetDevice(ctypes.byref(now))
     assert now.value == 0
 """)
+
+
+@pytest.mark.parametrize("schedule,padded", [(None, False), ("fixed", False), ("8,0,2048", True)])
+def test_banded_plan_is_timed_against_the_plan_it_stands_for(run, schedule, padded):
+    """The 3-D solve that band_speedup and PIPE_BAND_FASTEST compare with is that of the
+    plan the mesh would get: padded under a forced schedule."""
+    run("""
+h = ctypes.c_void_p()
+pipe.check(pipe.lib().pipe_green_plan_banded(24, 20, 48, 1 / 25, 1 / 21, .05, 1., 1., 0., 0., pipe.PREC_FP32 | 1, 48, 40,
+                                             0, 0, 2, 0., None, ctypes.byref(h)))
+assert info(h).xtile == 0
+assert ("xprod_kernel" in kernels()) == %r
+""" % padded, **({"PIPE_SCHEDULE": schedule} if schedule else {}))
