@@ -147,12 +147,8 @@ def batch_leg(pipe, torch, workloads, replays=20, warmup=3):
     man = workloads.batch_manifest()
     members = [workloads.batch_member(d) for d in man]
     log("[bench] batch: building %d FP32 and %d FP64 plans" % (len(members), len(members)))
-    # batch members: padded lengths per mesh shape chosen by the plan-time
-    # autotuner in throughput mode (timed once per shape); the FP64 plans of
-    # the plain sequential comparison keep the default lengths
     mk = lambda w, prec: pipe.GreenPlan(w.nx, w.ny, w.nz, w.hx, w.hy, w.hz, w.a, w.b, kind=w.kind,
-                                        precision=prec, mx=w.mx, my=w.my,
-                                        autotune="batch" if prec == "fp32" else False)
+                                        precision=prec, mx=w.mx, my=w.my)
     p32 = [mk(w, "fp32") for w in members]
     p64 = [mk(w, "fp64") for w in members]
     r32 = [torch.from_numpy(w.rho).to("cuda", torch.float32) for w in members]
@@ -181,34 +177,14 @@ def batch_leg(pipe, torch, workloads, replays=20, warmup=3):
     ref = [o.double().cpu().numpy() for o in o64]
     err = max(float(np.linalg.norm(g - r) / np.linalg.norm(r)) for g, r in zip(got, ref))
     model = sum(p.info.model_bytes for p in p32)
-    # the same solves' model bytes at the smallest padded lengths the Appendix
-    # allows (L >= 2n - 1, a supported 2^p 3^q; lz even with lz/2 >= nz): one
-    # plan per shape at those lengths, few modes (the bytes do not depend on them)
-    smooth = sorted(2 ** p * 3 ** q for p in range(11) for q in range(7) if 8 <= 2 ** p * 3 ** q <= 1024)
-    least = lambda need: next(v for v in smooth if v >= need)
-    per_shape = {}
-    for w in members:
-        if w.shape not in per_shape:
-            L = (least(2 * w.nx - 1), least(2 * w.ny - 1), 2 * least(w.nz))
-            q = pipe.GreenPlan(w.nx, w.ny, w.nz, w.hx, w.hy, w.hz, w.a, w.b, kind=w.kind, precision="fp32",
-                               mx=2, my=2, L=L)
-            per_shape[w.shape] = q.info.model_bytes
-            q.close()
-    model_min = sum(per_shape[w.shape] for w in members)
     n = len(members)
-    tuned = {}
-    for w, p in zip(members, p32):
-        tuned["%dx%dx%d" % w.shape] = "%dx%dx%d" % (p.info.lx, p.info.ly, p.info.lz)
     res = {"solves": n, "shapes": sorted({"%dx%dx%d" % w.shape for w in members}),
-           "autotuned_padded_lengths_fp32": tuned,
            "batched_fp32_solves_per_s": n / t_batch, "batched_fp32_ms_per_batch": t_batch * 1e3,
            "sequential_fp32_solves_per_s": n / t_seq32, "sequential_fp64_solves_per_s": n / t_seq64,
            "speedup_batched_fp32_over_sequential_fp64": t_seq64 / t_batch,
            "speedup_batched_fp32_over_sequential_fp32": t_seq32 / t_batch,
            "model_bytes_per_batch": model, "batched_model_GBps": model / t_batch / 1e9,
            "batched_hbm_frac": model / t_batch / 8e12,
-           "model_bytes_per_batch_smallest_lengths": model_min,
-           "batched_hbm_frac_smallest_lengths": model_min / t_batch / 8e12,
            "max_member_rel_l2_fp32_vs_fp64": err}
     b.close()
     for p in p32 + p64:
