@@ -27,9 +27,15 @@ METRIC = "open-pipe Poisson solves/s at 128x128x512 (FP32 vs FP64) + % HBM roofl
 HBM_PEAK_GBS = 8000.0
 PASS_NAMES = ["z_forward", "y_forward", "x_product", "y_inverse", "z_inverse"]
 KERNEL_NAMES = ["z_r2c_kernel", "strided_kernel<fwd>", "xprod_kernel", "strided_kernel<inv>", "z_c2r_kernel"]
-# the five kernels of a plan that solves in the sine modes of the cross-section
+# the kernels of a plan that solves in the sine modes of the cross-section: five, or
+# three where the middle ones are one launch over planes
 SINE_PASS_NAMES = ["x_sines", "y_sines", "z_sum", "y_sines_back", "x_sines_back"]
 SINE_KERNEL_NAMES = ["sine_kernel<fwd>", "sine_kernel<fwd>", "zexp_kernel", "sine_kernel<inv>", "sine_kernel<inv>"]
+PLANE_PASSES = [(0, "outer_sines", "sine_kernel<fwd>"), (1, "planes", "plane_kernel"),
+                (4, "outer_sines_back", "sine_kernel<inv>")]
+# a banded plan by padded transforms
+BAND_PASSES = [(0, "y_forward", "strided_pair_kernel<fwd>"), (1, "x_product", "xband_kernel"),
+               (2, "y_inverse", "strided_pair_kernel<inv>")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_three_bunch_cic.json")
 KERNEL_SOURCES = ["paper_1111_4971_amd/csrc/modal.hip", "paper_1111_4971_amd/csrc/passes.hip", "paper_1111_4971_amd/csrc/xprod.hip",
                   "paper_1111_4971_amd/csrc/pass_common.h", "paper_1111_4971_amd/csrc/fft_engine.h"]
@@ -47,9 +53,24 @@ def kernel_source_sha():
     return h.hexdigest()[:16]
 
 
-def pass_names(info):
-    """Names of a 3-D plan's five passes and their kernels (sine-mode plans have no x-pass tile)."""
-    return (SINE_PASS_NAMES, SINE_KERNEL_NAMES) if info.xtile == 0 else (PASS_NAMES, KERNEL_NAMES)
+def passes(info):
+    """(slot of the plan's pass times, name, kernel) of each kernel a solve launches."""
+    if info.band >= 0 and info.pass_bytes[4] == 0:
+        return BAND_PASSES
+    if info.xtile:
+        return list(zip(range(5), PASS_NAMES, KERNEL_NAMES))
+    if info.pass_bytes[2] == 0:
+        return PLANE_PASSES
+    z = "zconv_kernel" if info.band > 16 else "zband_kernel" if info.band >= 0 else SINE_KERNEL_NAMES[2]
+    return list(zip(range(5), SINE_PASS_NAMES, SINE_KERNEL_NAMES[:2] + [z] + SINE_KERNEL_NAMES[3:]))
+
+
+def pass_figures(info, pass_ms):
+    """Time, algorithmic bytes and their rate, per kernel of a solve."""
+    return {name: {"kernel": kernel, "ms": pass_ms[i], "model_bytes": info.pass_bytes[i],
+                   "GBps": info.pass_bytes[i] / (pass_ms[i] * 1e-3) / 1e9,
+                   "hbm_frac": info.pass_bytes[i] / (pass_ms[i] * 1e-3) / 1e9 / HBM_PEAK_GBS}
+            for i, name, kernel in passes(info)}
 
 
 def measured_traffic(leg, name):
@@ -111,10 +132,10 @@ def time_leg(pipe, torch, wl, precision, steps, warmup):
     ms_events = (time.perf_counter() - t2) * 1e3 / steps
     pass_ms, n = plan.timing_stop()
     out = phi.double().cpu().numpy()
-    dom = max(range(5), key=lambda i: pass_ms[i])
-    achieved = info.pass_bytes[dom] / (pass_ms[dom] * 1e-3) / 1e9
-    names, kernels = pass_names(info)
-    traffic = measured_traffic(precision, names[dom])
+    figures = pass_figures(info, pass_ms)
+    dom = max(figures, key=lambda name: figures[name]["ms"])
+    top = figures[dom]
+    traffic = measured_traffic(precision, dom)
     leg = {
         "value": steps / (t1 - t0),
         "ms_per_step": ms_step,
@@ -127,14 +148,10 @@ def time_leg(pipe, torch, wl, precision, steps, warmup):
         "model_bytes_per_solve": info.model_bytes,
         "model_GBps_whole_solve": info.model_bytes / (ms_step * 1e-3) / 1e9,
         "hbm_frac_whole_solve": info.model_bytes / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
-        "passes": {names[i]: {"kernel": kernels[i], "ms": pass_ms[i],
-                              "model_bytes": info.pass_bytes[i],
-                              "GBps": info.pass_bytes[i] / (pass_ms[i] * 1e-3) / 1e9,
-                              "hbm_frac": info.pass_bytes[i] / (pass_ms[i] * 1e-3) / 1e9 / HBM_PEAK_GBS}
-                   for i in range(5)},
-        "roofline": {"bound": "hbm", "kernel": kernels[dom], "achieved": achieved, "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "algorithmic_bytes_per_launch": info.pass_bytes[dom], "avg_launch_ms": pass_ms[dom]},
+        "passes": figures,
+        "roofline": {"bound": "hbm", "kernel": top["kernel"], "achieved": top["GBps"], "peak": HBM_PEAK_GBS,
+                     "unit": "GB/s", "frac": top["hbm_frac"], "traffic": traffic,
+                     "algorithmic_bytes_per_launch": top["model_bytes"], "avg_launch_ms": top["ms"]},
     }
     plan.close()
     return leg, out
@@ -274,21 +291,20 @@ def band_leg(pipe, torch, steps=50, tol=1e-6):
             plan = pipe.GreenPlan(wl.nx, wl.ny, wl.nz, wl.hx, wl.hy, wl.hz, wl.a, wl.b, kind=wl.kind,
                                   precision=prec, mx=wl.mx, my=wl.my)
             ms_full, pm, y = timed(plan, x)
+            kernels = pass_figures(plan.info, pm)
             plan.close()
             if ref is None:
                 ref = y
-            r.setdefault("full", {})[prec] = {"ms_per_solve": ms_full, "kernel_ms": pm}
+            r.setdefault("full", {})[prec] = {"ms_per_solve": ms_full, "kernels": kernels}
             for nb in bands:
                 log("[bench] band %s %s: N = %s" % (key, prec, nb))
                 plan = pipe.GreenPlan(wl.nx, wl.ny, wl.nz, wl.hx, wl.hy, wl.hz, wl.a, wl.b, kind=wl.kind,
                                       precision=prec, mx=wl.mx, my=wl.my, band=nb, band_tol=tol)
                 ms, pm, y = timed(plan, x)
-                pb = plan.info.pass_bytes
                 e = r.setdefault("N_auto" if nb == "auto" else "N%d" % nb, {})
                 e["N"] = plan.band
-                e[prec] = {"ms_per_solve": ms, "kernel_ms": pm[:3], "speedup_over_full": ms_full / ms,
+                e[prec] = {"ms_per_solve": ms, "kernels": pass_figures(plan.info, pm), "speedup_over_full": ms_full / ms,
                            "build_time_ratio_3d_over_banded": plan.info.band_speedup,
-                           "x_pass_GBps": pb[1] / (pm[1] * 1e-3) / 1e9,
                            "rel_max_vs_full_fp64": float(np.max(np.abs(y - ref)) / np.max(np.abs(ref)))}
                 plan.close()
                 if nb == "auto":
@@ -368,9 +384,7 @@ def free_leg(pipe, torch, wl, steps=100):
         info = plan.info
         res[prec] = {"ms_per_solve": ms, "solves_per_s": 1e3 / ms, "build_ms": plan.info.build_ms,
                      "spectra_bytes": info.spectra_bytes,
-                     "passes": {PASS_NAMES[i]: {"ms": pass_ms[i], "model_bytes": info.pass_bytes[i],
-                                                "hbm_frac": info.pass_bytes[i] / (pass_ms[i] * 1e-3) / 1e9
-                                                / HBM_PEAK_GBS} for i in range(5)}}
+                     "passes": pass_figures(info, pass_ms)}
         plan.close()
     return res
 
