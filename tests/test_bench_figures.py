@@ -35,3 +35,11 @@ def test_every_kernel_has_its_own_figures(name):
         assert f["ms"] == ms[i] and f["model_bytes"] == nbytes[i] * 1e6
         assert f["GBps"] == pytest.approx(nbytes[i] * 1e6 / (ms[i] * 1e-3) / 1e9)
         assert f["hbm_frac"] == pytest.approx(f["GBps"] / 8000)
+
+
+def test_lengths_are_given_where_they_are_transformed():
+    sched = dict(apad=16, zblocks=2048, xnt=0, a1pad=0, lx=256, ly=256, lz=1024)
+    sine = bench.plan_lengths(SimpleNamespace(xtile=0, **sched))
+    assert sine == {"solver": "sine modes", "padded_lengths": None, "schedule": None}
+    padded = bench.plan_lengths(SimpleNamespace(xtile=8, **sched))
+    assert padded["padded_lengths"] == [256, 256, 1024] and padded["schedule"]["x_tile"] == 8
