@@ -1231,7 +1231,7 @@ hipError_t launch_sine(const SineAxis& ax, bool inverse, const void* in, void* o
 
 // Transform lengths of the z convolution (kZconvLengths).
 #define PIPE_FOR_EACH_ZCONV_N(X) \
-    X(8) X(16) X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(768) X(1024)
+    X(24) X(32) X(48) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(768) X(1024)
 
 // Blocks of a kernel that run on one CU at once.  The persistent z convolution gets
 // exactly as many as run (a second, partly filled wave of blocks costs more than the
@@ -1373,7 +1373,7 @@ hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int 
         hipLaunchKernelGGL((zband_kernel<real, N_>), grid, block, 0, s, (const real*)in, (real*)out, wv, total, \
                            (const real*)table);                                                               \
         return hipGetLastError();
-        X(0) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
+        X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16)
 #undef X
     }
     return hipErrorInvalidValue;

@@ -214,8 +214,8 @@ hipError_t launch_sine(const SineAxis& ax, bool inverse, const void* in, void* o
                        long in_es, long out_ss, long out_es, long nslabs, bool user_vec, hipStream_t s,
                        const GroupArgs* group = nullptr, int ngroup = 1);
 // Half lengths of the z convolution: those whose line lies inside one wavefront
-// (must match PIPE_FOR_EACH_ZCONV_N).
-constexpr int kZconvLengths[] = {8, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
+// (must match PIPE_FOR_EACH_ZCONV_N); lines of up to 16 are always summed in a plane's launch.
+constexpr int kZconvLengths[] = {24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
 inline int zconv_length(int n) {
     for (int v : kZconvLengths)
         if (v >= n) return v;
@@ -297,7 +297,8 @@ hipError_t launch_modal_band(void* out, int real_bytes, const SineAxis& ax, cons
                              double a, double b, double hz, int igf, double scale, int pitch, int lead, hipStream_t st);
 // out_k = sum over |d| <= nb of table[line][|d|] in_{k+d} on nlines lines of nz
 // values, pitch apart (a multiple of a 16-byte vector; values beyond nz are zero in
-// the input and unspecified in the output); in != out, nb <= kModalBandMax.
+// the input and unspecified in the output); in != out, 1 <= nb <= kModalBandMax (a sum over
+// the plane alone always goes in the planes' launch).
 constexpr int kModalBandMax = 16;
 template <typename real>
 hipError_t launch_zband(const void* in, void* out, long pitch, long nlines, int nb, const void* table, hipStream_t s);
