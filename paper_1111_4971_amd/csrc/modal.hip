@@ -1172,11 +1172,16 @@ template <typename real, bool INV, bool UV>
 static hipError_t launch_sine_dir(SineArgs a, hipStream_t s, const GroupArgs* group, int ngroup) {
     if (a.rt <= 8 && a.kb <= kSineBlocks) {
         // one column a lane where that makes few tiles: the products of a tile are one wave's
-        // serial work, a block's matrix rows the price (solves, us: 247x17x47 FP32 44 -> 27,
-        // 104x19x85 FP32 34.8 -> 29.4, 70x40x75 FP64 33.6 -> 30.6; up to 512 tiles 250x100x60
-        // FP32 50.9 -> 45.0, 120x120x60 FP64 44.7 -> 46.1; up to 1024 64x64x256 FP64 44.5 ->
-        // 40.9, FP32 30.8 -> 28.1, 160x160x64 FP32 47.0 -> 50.4)
-        const int v = sine_V<real>(a.kb), few = a.kb <= 2 ? 1024 : sizeof(real) == 4 ? 512 : 256;
+        // serial work, a block's matrix rows the price.  Tiles up to which it pays, by depth in
+        // blocks (whole solves in us, wide -> narrow; in brackets the tiles of a pass): one block
+        // FP32 32x32x250 (500) 23.3 -> 21.9, 30x31x500 (969) 25.6 -> 28.5, FP64 32x32x128 (256)
+        // 20.5 -> 20.1, 32x32x250 26.6 -> 27.2 (few modes, more rows: within 3 % either way, FP64
+        // 20 modes 128x128x100 (800) 32.4 -> 33.0, 200x200x60 (750) 41.6 -> 40.1); two FP32 64x64x256 (1024) 31.0 -> 28.2, 64x64x640
+        // (2560) 46.2 -> 42.1, 64x64x1000 (4000) 54.5 -> 57.2, FP64 64x64x384 (1536) 47.6 -> 45.1,
+        // 40x40x720 (1800) 46.8 -> 48.2, 64x64x500 (2000) 54.3 -> 53.1; more FP32 250x100x60
+        // (375, 938) 50.9 -> 45.0, 160x160x64 (640) 47.0 -> 50.4, FP64 120x120x60 (450) 44.7 -> 46.1.
+        const bool fp32 = sizeof(real) == 4;
+        const int v = sine_V<real>(a.kb), few = a.kb == 2 ? (fp32 ? 2560 : 1536) : fp32 ? 512 : 256;
         if (v > 1 && (a.ngroups * v + 15) / 16 * ngroup <= few) {
             a.wv *= v;
             a.ngroups *= v;

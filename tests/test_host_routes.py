@@ -66,12 +66,13 @@ def plan(shape, flags=pipe.PREC_FP32, L=(0, 0, 0), shrink=1.0):
     return h
 
 
-def solve_kernels(h):
-    """The kernels of one solve."""
-    i = info(h)
+def solve_kernels(h, log=None):
+    """The kernels of one solve; the runtime's own lines go to log."""
     buf = [ctypes.c_void_p((k + 1) << 40) for k in range(3)]       # never touched: kernels do nothing
     calls()
     pipe.check(pipe.lib().pipe_poisson_solve(h, *buf, None))
+    if log is not None:
+        log.append(_fake.fake_hip_log().decode())
     return kernels()
 
 
@@ -143,3 +144,17 @@ pipe.check(pipe.lib().pipe_green_plan_banded(24, 20, 48, 1 / 25, 1 / 21, .05, 1.
 assert info(h).xtile == 0
 assert ("xprod_kernel" in kernels()) == %r
 """ % padded, **({"PIPE_SCHEDULE": schedule} if schedule else {}))
+
+
+@pytest.mark.parametrize("shape,prec,columns", [
+    ((32, 32, 250), "fp32", 1), ((30, 31, 500), "fp32", 4), ((32, 32, 128), "fp64", 1), ((30, 31, 500), "fp64", 2),
+    ((64, 64, 640), "fp32", 1), ((64, 64, 1000), "fp32", 4), ((64, 64, 384), "fp64", 1), ((64, 64, 500), "fp64", 2)])
+def test_sine_tiles_by_depth(run, shape, prec, columns):
+    """Columns a lane of the sine passes, on both sides of the limits of one and two blocks of
+    depth (tiles of one column a lane: 500, 969, 256, 969; 2560, 4000, 1536, 2000)."""
+    run("""
+h = plan(%r, pipe.PREC_FP%s)
+solve_kernels(h, last := [])
+got = {int(v) for v in re.findall(r"sine_kernelI[fd]Lb[01]ELi(\\d)", last[0])}
+assert got == {%d}, got
+""" % (shape, prec[2:], columns))
