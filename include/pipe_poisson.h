@@ -88,7 +88,8 @@ typedef struct pipe_plan_info {
     double model_bytes;      /* algorithmic HBM bytes of one solve (all passes)             */
     double pass_bytes[5];    /* the same per pass: z-forward, y-forward, x+product,         */
                              /* y-inverse, z-inverse; in the sine modes x, y sines, z sum,  */
-                             /* y, x sines back                                             */
+                             /* y, x sines back, or, where the middle three are one launch, */
+                             /* sines of one axis, that launch, 0, 0, sines back            */
     double build_ms;         /* wall time of the plan build (Green evaluation + spectra)    */
     double tune_ms;          /* PIPE_AUTOTUNE: the chosen lengths' measured ms per solve  */
                              /* (0 = taken from the cache; -1 = not tuned)                */
@@ -139,7 +140,9 @@ pipe_status_t pipe_green_plan(int nx, int ny, int nz, double hx, double hy, doub
  * to rounding, no offset, likewise in y, nx, ny <= 512) with all lengths left
  * at 0 is solved in the discrete sine modes of the cross-section instead, where
  * the four terms are one real factor per mode and nothing is padded in x and y:
- * the same potential to rounding, in about a third of the memory traffic.  Such
+ * the same potential to rounding, in about a third of the memory traffic.  A node
+ * on a wall has no part in any mode: its charge is not read (whatever it is, NaN
+ * included) and its potential is 0 exactly.  Such
  * a plan reports the lengths and workspace the padded transform would have, and
  * 0 for the launch schedule (xtile, apad, zblocks, xnt, a1pad); explicit lengths,
  * lengths to be tuned (PIPE_AUTOTUNE*) or a forced PIPE_SCHEDULE keep the padded
@@ -389,6 +392,7 @@ pipe_status_t pipe_plan_spectra(pipe_plan_t plan, void* out_device, void* hip_st
  * pipe_poisson_solve_timed -- pipe_poisson_solve preceded and followed by
  * HIP events around each of its five kernels on hip_stream; pass_ms[5]
  * receives the elapsed time of each kernel of this call (blocks until done).
+ * A pass whose pass_bytes is 0 has no kernel: its entry is the events' own time.
  */
 pipe_status_t pipe_poisson_solve_timed(pipe_plan_t plan, const void* rho, void* phi,
                                        void* workspace, void* hip_stream, float* pass_ms);

@@ -15,10 +15,11 @@
 // where the planes of one axis fit LDS, M2 to M4 are one launch [plane] and the
 // longer axis goes first and last.  Nothing is padded in x and y: 10 n values move instead of the 35 n of the
 // padded transform (n = nx ny nz, the spectra included).  nzp is nz rounded up
-// to a 16-byte vector.  Whole solves, padded transform -> sine modes: 128x128x512
-// FP32 235 -> 103 us, FP64 456 -> 162 us; 256x256x1024 FP32 1853 -> 768 us;
-// 64x64x256 FP64 74 -> 40 us; 32x32x32 FP64 30 -> 19 us; errors against 64 bits no larger (FP32 1.4e-7
-// against 2.2e-7).
+// to a 16-byte vector.  A node on a wall carries no mode: its charge is not read and its
+// potential is zero.  Whole solves, padded transform -> sine modes: 128x128x512
+// FP32 234 -> 103 us, FP64 455 -> 164 us; 256x256x1024 FP32 1854 -> 772 us;
+// 64x64x256 FP64 74 -> 37 us; 32x32x32 FP64 27 -> 22 us; errors against 64 bits no larger (FP32 1.4e-7
+// against 2.1e-7 at 128x128x512).
 #include <algorithm>
 
 #include "pass_common.h"

@@ -320,9 +320,10 @@ int modal_nzp(const pipe_plan_s* p) {
 bool modal_direct(const pipe_plan_s* p) { return p->band >= 0 && p->band <= kModalBandMax; }
 
 // Workspace of a solve.  A sine-mode plan uses the two arrays (nmx, ny, nzp) and
-// (nmx, nmy, nzp), a banded one a third like the second, which always fit (at most
-// 2 nx ny (nz + 3) reals against 6 nx ny nz, 3 nx ny (nz + 3) against 4 nx ny (nz +
-// 32)); it reports the padded transform's size all the same, so that which
+// (nmx, nmy, nzp), a banded one a third like the second, which always fit: at most
+// 2 nx ny (nz + 3) reals against 2 nx ny nh + 2 nx ly nh >= 6 nx ny nh, where the
+// default lengths have ly >= 2 ny and nh >= max(nz, 8); and 3 nx ny (nz + 3) against
+// 4 nx ly (nz/2 + 16) >= 4 nx ny (nz + 32).  It reports the padded transform's size all the same, so that which
 // meshes the fixed scratch accepts does not depend on the algorithm.
 size_t plan_ws_bytes(const pipe_plan_s* p) {
     const size_t cb = 2 * (size_t)p->rb;

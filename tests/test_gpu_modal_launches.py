@@ -12,6 +12,13 @@ pytestmark = pytest.mark.gpu
 A, B, HZ = 1.2, 0.9, 0.05
 
 
+@pytest.fixture(scope="module", autouse=True)
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available()
+    return torch
+
+
 def _geometry(shape, wall=(False, False)):
     return A / (shape[0] + (not wall[0])), B / (shape[1] + (not wall[1])), HZ, A, B
 
@@ -154,3 +161,16 @@ def test_sine_tile_widths_match_the_padded_transform(shape, prec):
     got, ref = gpu_solve(p, rho), gpu_solve(q, rho)
     p.close(), q.close()
     assert rel_l2(got, ref) <= 2 * TOL[prec] and rel_max(got, ref) <= 2 * TOL[prec], rel_l2(got, ref)
+
+
+@pytest.mark.parametrize("shape", [(33, 18, 40), (130, 100, 90), (300, 5, 20)])
+def test_wall_nodes_are_not_read(torch_cuda, shape):
+    """Charge on the walls changes nothing, whatever it is, and the potential there is 0."""
+    torch = torch_cuda
+    wall = (True, True)
+    p = _plan(shape, "fp64", wall, _modes(shape, (2, 2), wall))
+    x = torch.from_numpy(np.random.default_rng(3).standard_normal(shape)).to("cuda")
+    log("wall nodes %s" % (shape,))
+    ref = p.solve(x)
+    x[-1], x[:, -1] = float("nan"), float("inf")
+    assert torch.equal(p.solve(x), ref) and not ref[-1].any() and not ref[:, -1].any()
