@@ -332,8 +332,7 @@ def same_plan_leg(pipe, torch, wl, members=8, replays=20):
     """Many charges, one cached Green function (Sec. 2 after Eq. 10: the spectra
     are computed once and reused): the benchmark plan repeated `members` times
     in one batch, each member with its own charge (the benchmark charge shifted
-    along z by k planes).  The fused x pass runs the members of one (kz tile, ky)
-    back to back, so the spectra tile comes from L2 for all but the first."""
+    along z by k planes)."""
     import numpy as np
     res = {"members": members}
     for prec in ("fp32", "fp64"):
